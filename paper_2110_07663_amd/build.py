@@ -42,6 +42,7 @@ FILE_FLAGS = {
     # matrix-core FDM: accumulate in ordinary vector registers (the results feed
     # LDS stores and further products directly, no moves out of AGPRs)
     "fdm_mf32.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+    "fdm_mf64.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
 }
 
 

@@ -661,8 +661,13 @@ static void fdm_p(const Ctx &c, const Level &L, const T *r, T *z, bool asm_mode,
     T *box = sizeof(T) == 8 ? (T *)L.box64 : (T *)L.box32;
     if (!box) fail(SEM_EINVAL, "ASM box buffer was not built");
     for (int k = 0; k < nv; ++k) {  // one box buffer: right sides in turn
-      fdm_launch<P, T, true>(c, L, r + k * L.nloc, rs ? rs + k * L.nloc : nullptr, S, lam, W, box,
-                             s, 1);
+      const T *rk = r + k * L.nloc, *rsk = rs ? rs + k * L.nloc : nullptr;
+      bool mc = false;
+      if constexpr (sizeof(T) == 8) {
+        mc = fdm_mf64_supported(c, P, true);
+        if (mc) launch_fdm_mf64(c, L, rk, box, true, s, 1, rsk);
+      }
+      if (!mc) fdm_launch<P, T, true>(c, L, rk, rsk, S, lam, W, box, s, 1);
       launch_asm_sum<T>(c, L, box, z + k * L.nloc, s);
     }
     return;
@@ -674,6 +679,12 @@ static void fdm_p(const Ctx &c, const Level &L, const T *r, T *z, bool asm_mode,
     }
   }
   if (xin) fail(SEM_EINVAL, "FDM: this kernel needs assembled inputs");
+  if constexpr (sizeof(T) == 8) {
+    if (fdm_mf64_supported(c, P, false)) {
+      launch_fdm_mf64(c, L, r, z, false, s, nv, rs);
+      return;
+    }
+  }
   fdm_launch<P, T, false>(c, L, r, rs, S, lam, W, z, s, nv);
 }
 

@@ -263,6 +263,7 @@ struct Ctx {
   bool fdm_group = true;  // p <= 3: several elements' boxes per workgroup of 256 threads
   bool fdm_mfma1 = false; // first matrix-core FDM form (LDS FP32 box) instead of the second
   bool fdm_mf32 = true;   // FP32 RAS local solves on the matrix cores (fdm_mf32.hip)
+  bool fdm_mf64 = true;   // FP64 Schwarz local solves on the matrix cores (fdm_mf64.hip)
   int fdm_mf32_chain = 1; // elements per wavefront there (1 or 2), next one's loads ahead
   bool fdm_mf16 = true;   // FP16 / BF16 RAS operands in that kernel's 4x4x4 form
   bool fdm_xstep = true;  // that kernel takes the x step of A's gather-scatter as it reads
@@ -407,6 +408,12 @@ void launch_fdm_mfma(const Ctx &c, const Level &L, const float *r, float *z, boo
                      int prec, hipStream_t s, int nv = 1);
 template <typename T>
 void launch_asm_sum(const Ctx &c, const Level &L, const T *box, T *z, hipStream_t s);
+
+// fdm_mf64.hip: FP64 RAS and ASM local solves on the matrix cores (ASM: z = the
+// boxes [E][pb^3])
+bool fdm_mf64_supported(const Ctx &c, int p, bool asm_mode);
+void launch_fdm_mf64(const Ctx &c, const Level &L, const double *r, double *z, bool asm_mode,
+                     hipStream_t s, int nv, const double *rs);
 
 // fdm_mf32.hip: FP32 RAS local solves on the matrix cores (2 <= p <= 9, no
 // floating box)

@@ -354,6 +354,8 @@ static void init_ctx(Ctx &c, const sem_mesh *m, int p, const int8_t *bc, const s
   c.fdm_mfma1 = fm && fm[0] == '1';
   const char *f32 = getenv("SEM_FDM_MF32");
   c.fdm_mf32 = !(f32 && f32[0] == '0');
+  const char *f64 = getenv("SEM_FDM_MF64");
+  c.fdm_mf64 = !(f64 && f64[0] == '0');
   const char *f16 = getenv("SEM_FDM_MF16");
   c.fdm_mf16 = !(f16 && f16[0] == '0');
   const char *fch = getenv("SEM_FDM_MF32_CHAIN");
