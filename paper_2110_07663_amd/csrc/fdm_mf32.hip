@@ -1,6 +1,9 @@
-// RAS local solves by the fast diagonalisation method (Sec. 2.2.2, eqs. 8-9)
-// on the matrix cores: FP32 operands, or FP16 / BF16 operands with FP32
-// accumulation (k_fdm_mf16, the same kernel forms with v_mfma_f32_4x4x4).
+// Schwarz local solves by the fast diagonalisation method (Sec. 2.2.2, eqs. 8-9)
+// on the matrix cores: RAS with FP32 operands, or FP16 / BF16 operands with FP32
+// accumulation (k_fdm_mf16, the same kernel forms with v_mfma_f32_4x4x4), and ASM
+// with FP32 operands, which keeps the whole box (each backward pass ends on 10 nodes
+// instead of 8 at p = 7; 12.0 us for 2002 elements with the deferred steps
+// taken as it reads, where the vector kernel took 13.6 us and the two passes 6).
 //
 // Each of the six 1D contractions of the (p+3)^3 box is a product of the box
 // lines with a (p+3)x(p+3) factor: out[line][m] = sum_k in[line][k] S[k][m].
@@ -142,24 +145,26 @@ struct RasW {
 template <int P>
 constexpr bool kRasWComputed = P >= 4;
 
-template <int P>
+// AS: the whole box is kept (additive Schwarz), else the element's own nodes
+template <int P, bool AS = false>
 struct Mf {
   static constexpr int PB = P + 3, N = P + 1, N3 = N * N * N;
   static constexpr int NL = PB * PB, SF = (NL + 63) / 64;  // forward lines, slots
   static constexpr int MG = (PB + 3) / 4;                  // groups of 4 modes
-  static constexpr int KG = (N + 3) / 4;                   // groups of 4 kept nodes
+  static constexpr int NK = AS ? PB : N, K0 = AS ? 0 : 1;  // kept nodes, the first of them
+  static constexpr int KG = (NK + 3) / 4;                  // groups of 4 kept nodes
   static constexpr int LS = (PB + 3) / 4 * 4;              // LDS line stride
   static constexpr int QF = PB * MG, QB = PB * KG;         // A operands per pass
   static constexpr int UF = (QF + 15) / 16, UB = (QB + 15) / 16;
-  static constexpr int NLY = PB * N, SY = (NLY + 63) / 64;  // backward y lines (kept planes)
-  static constexpr int NLX = N * N, SX = (NLX + 63) / 64;   // backward x lines (kept rows)
+  static constexpr int NLY = PB * NK, SY = (NLY + 63) / 64;  // backward y lines (kept planes)
+  static constexpr int NLX = NK * NK, SX = (NLX + 63) / 64;  // backward x lines (kept rows)
   static constexpr int BUF = NL * LS;                        // floats per wavefront
   static constexpr int WAVES = 4;
   // 16-bit operands: k in groups of four (forward: the line's nodes; backward:
   // the modes), one register pair of A operands per direction and pass kind
   static constexpr int K4 = (PB + 3) / 4;
   static constexpr int QF16 = K4 * MG, QB16 = K4 * KG;
-  static_assert(QF16 <= 16 && QB16 <= 16, "16-bit A operands exceed one broadcast register");
+  static_assert(AS || (QF16 <= 16 && QB16 <= 16), "16-bit A operands exceed one broadcast register");
   static_assert(K4 == MG, "16-bit forward pairs: k groups and mode groups both cover PB");
 };
 
@@ -207,11 +212,11 @@ __device__ __attribute__((always_inline)) inline void mf_forward(const float *A,
     }
 }
 
-// backward contraction to the kept nodes: acc[g][i] = sum_m S[1 + 4g + i][m] h[m]
-template <int P>
+// backward contraction to the kept nodes: acc[g][i] = sum_m S[K0 + 4g + i][m] h[m]
+template <int P, bool AS = false>
 __device__ __attribute__((always_inline)) inline void mf_backward(const float *A, const float *h,
                                                                   mf4_t *acc) {
-  using F = Mf<P>;
+  using F = Mf<P, AS>;
 #pragma unroll
   for (int g = 0; g < F::KG; ++g) acc[g] = mf4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -297,9 +302,9 @@ __device__ inline void mf_sync() {
 // rows on the element's y-faces (own rows j = 0, p of the element and of its
 // z-neighbours) also read the y-neighbour's copy of the row, of its end nodes'
 // x-partners and of the halo nodes beside it, and add them (y, then x).
-template <int P, bool RS, int XS, bool YS>
+template <int P, bool RS, int XS, bool YS, bool AS = false>
 struct MfIn {
-  using F = Mf<P>;
+  using F = Mf<P, AS>;
   float own[F::SF][F::N], lft[F::SF], rgt[F::SF];
   float sown[RS ? F::SF : 1][RS ? F::N : 1], slft[RS ? F::SF : 1], srgt[RS ? F::SF : 1];
   float xlp[XS ? F::SF : 1], xrp[XS ? F::SF : 1];  // x-partner copies of nodes 0 and p
@@ -323,13 +328,13 @@ struct BufU2 {
   }
 };
 
-template <int P, bool RS, int XS, bool YS, int OP = kOpF32>
+template <int P, bool RS, int XS, bool YS, int OP = kOpF32, bool AS = false>
 __device__ __attribute__((always_inline)) inline void mf_load(
-    MfIn<P, RS, XS, YS> &in, int64_t e, int nex, int ney, int nez, const BufF32 &r, const BufF32 &rs,
+    MfIn<P, RS, XS, YS, AS> &in, int64_t e, int nex, int ney, int nez, const BufF32 &r, const BufF32 &rs,
     int64_t eb, const float *__restrict__ Sg, const float *__restrict__ lamg,
     const RasW &W, int lane, const uint32_t *__restrict__ A16 = nullptr,
     const float *__restrict__ ssc = nullptr) {
-  using F = Mf<P>;
+  using F = Mf<P, AS>;
   constexpr int PB = F::PB, N = F::N, N3 = F::N3, MG = F::MG, KG = F::KG;
   if constexpr (OP != kOpF32) {
     // 16-bit A operands, packed at setup in lane order (k_fdm_mf16_pack): the
@@ -358,8 +363,8 @@ __device__ __attribute__((always_inline)) inline void mf_load(
     }
 #pragma unroll
     for (int u = 0; u < F::UB; ++u) {
-      const int q = 16 * u + qb, m = q / KG, k = 1 + 4 * (q % KG) + i;
-      const uint32_t at = q < F::QB && k <= N ? (uint32_t)(k * PB + m) * 4 : kOutside;
+      const int q = 16 * u + qb, m = q / KG, k = F::K0 + 4 * (q % KG) + i;
+      const uint32_t at = q < F::QB && k < F::K0 + F::NK ? (uint32_t)(k * PB + m) * 4 : kOutside;
       in.Ab[2][u] = Se.ld(at + 2 * PB * PB * 4);  // (x and y: loaded by the solve)
     }
   }
@@ -484,19 +489,19 @@ __device__ __attribute__((always_inline)) inline void mf_load(
 // 85 for the x/y-step form, 6 wavefronts per SIMD instead of 5): the y and x
 // backward A operands, the 16-bit forms' factor scales s_d, and the RAS
 // weights of the output rows
-template <int P>
+template <int P, bool AS = false>
 struct MfLate {
-  using F = Mf<P>;
+  using F = Mf<P, AS>;
   float Ab[2][F::UB];  // FP32 operands
   u2_t Ab16[2];        // 16-bit operands
   float ssc[3];
-  mf4_t wrow[F::SX][F::KG];
+  mf4_t wrow[AS ? 1 : F::SX][AS ? 1 : F::KG];
 };
-template <int P, int OP>
+template <int P, int OP, bool AS = false>
 __device__ __attribute__((always_inline)) inline void mf_load_late(
-    MfLate<P> &lt, int64_t e, const float *__restrict__ Sg, const RasW &W,
+    MfLate<P, AS> &lt, int64_t e, const float *__restrict__ Sg, const RasW &W,
     const uint32_t *__restrict__ A16, const float *__restrict__ ssc, int lane) {
-  using F = Mf<P>;
+  using F = Mf<P, AS>;
   constexpr int PB = F::PB, N = F::N, N3 = F::N3, KG = F::KG;
   if constexpr (OP != kOpF32) {
     constexpr int NF = 4 * F::QF16, NE = 4 * (F::QF16 + F::QB16);
@@ -511,13 +516,14 @@ __device__ __attribute__((always_inline)) inline void mf_load_late(
     const int i = lane & 3, qb = lane >> 2;
 #pragma unroll
     for (int u = 0; u < F::UB; ++u) {
-      const int q = 16 * u + qb, m = q / KG, k = 1 + 4 * (q % KG) + i;
-      const uint32_t at = q < F::QB && k <= N ? (uint32_t)(k * PB + m) * 4 : kOutside;
+      const int q = 16 * u + qb, m = q / KG, k = F::K0 + 4 * (q % KG) + i;
+      const uint32_t at = q < F::QB && k < F::K0 + F::NK ? (uint32_t)(k * PB + m) * 4 : kOutside;
 #pragma unroll
       for (int d = 0; d < 2; ++d) lt.Ab[d][u] = Se.ld(at + d * PB * PB * 4);
     }
   }
-  if constexpr (kRasWComputed<P>) {
+  if constexpr (AS) {  // the overlap sum weights the boxes
+  } else if constexpr (kRasWComputed<P>) {
     int64_t ex, ey, ez;
     elem_coords(e, W.nex, W.ney, ex, ey, ez);
 #pragma unroll
@@ -557,13 +563,16 @@ __device__ __attribute__((always_inline)) inline void mf_load_late(
 // eigenvalue-scaled tensor likewise before the backward passes (the output
 // then takes both powers of two back); BF16 keeps FP32's exponent range and
 // needs neither.
-template <int P, bool RS, int XS, bool YS, bool XF, int OP = kOpF32>
+// AS: z receives the whole box, [E][PB^3].
+template <int P, bool RS, int XS, bool YS, bool XF, int OP = kOpF32, bool AS = false>
 __device__ __attribute__((always_inline)) inline void mf_solve(
-    const MfIn<P, RS, XS, YS> &in, int64_t e, const float *__restrict__ lamg, float *__restrict__ z,
+    const MfIn<P, RS, XS, YS, AS> &in, int64_t e, const float *__restrict__ lamg, float *__restrict__ z,
     float *buf, int lane, float *xfx, int wave, const float *__restrict__ Sg,
     const RasW &W, const uint32_t *__restrict__ A16 = nullptr,
     const float *__restrict__ ssc = nullptr) {
-  using F = Mf<P>;
+  using F = Mf<P, AS>;
+  static_assert(!AS || (!XF && OP == kOpF32), "additive Schwarz: FP32, no x-face sums");
+  constexpr int NK = F::NK;
   constexpr int PB = F::PB, N = F::N, N3 = F::N3, LS = F::LS, MG = F::MG, KG = F::KG;
   const float *le = lamg + e * 3 * PB;
   float v[F::SF][PB];
@@ -625,8 +634,8 @@ __device__ __attribute__((always_inline)) inline void mf_solve(
     else
       mf_forward<P>(in.Af[0], v[s], acc[s]);
   }
-  MfLate<P> lt;
-  mf_load_late<P, OP>(lt, e, Sg, W, A16, ssc, lane);
+  MfLate<P, AS> lt;
+  mf_load_late<P, OP, AS>(lt, e, Sg, W, A16, ssc, lane);
 #pragma unroll
   for (int s = 0; s < F::SF; ++s) {
     const int l = 64 * s + lane;
@@ -701,7 +710,7 @@ __device__ __attribute__((always_inline)) inline void mf_solve(
       float h[PB];
 #pragma unroll
       for (int m = 0; m < PB; ++m) h[m] = acc[s][m >> 2][m & 3] * mf_inv(lxy + le[2 * PB + m]);
-      mf_backward<P>(in.Ab[2], h, bk[s]);
+      mf_backward<P, AS>(in.Ab[2], h, bk[s]);
     }
   }
   mf_sync();
@@ -714,7 +723,7 @@ __device__ __attribute__((always_inline)) inline void mf_solve(
       for (int g = 0; g < KG; ++g)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          if (4 * g + i < N) buf[(a + PB * (4 * g + i)) * LS + b] = bk[s][g][i];
+          if (4 * g + i < NK) buf[(a + PB * (4 * g + i)) * LS + b] = bk[s][g][i];
     }
   }
   mf_sync();
@@ -732,7 +741,7 @@ __device__ __attribute__((always_inline)) inline void mf_solve(
     if constexpr (OP != kOpF32)
       mf16_backward<P, OP, false>(lt.Ab16[1], w[s], 1.f, by[s]);
     else
-      mf_backward<P>(lt.Ab[1], w[s], by[s]);
+      mf_backward<P, AS>(lt.Ab[1], w[s], by[s]);
   }
   mf_sync();
 #pragma unroll
@@ -744,7 +753,7 @@ __device__ __attribute__((always_inline)) inline void mf_solve(
       for (int g = 0; g < KG; ++g)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          if (4 * g + i < N) buf[(4 * g + i + N * k) * LS + a] = by[s][g][i];
+          if (4 * g + i < NK) buf[(4 * g + i + NK * k) * LS + a] = by[s][g][i];
     }
   }
   mf_sync();
@@ -768,9 +777,14 @@ __device__ __attribute__((always_inline)) inline void mf_solve(
 #pragma unroll
       for (int g = 0; g < KG; ++g) o[s][g] = lt.wrow[s][g] * (bx[g] * osc);
     } else {
-      mf_backward<P>(lt.Ab[0], u, bx);
+      mf_backward<P, AS>(lt.Ab[0], u, bx);
 #pragma unroll
-      for (int g = 0; g < KG; ++g) o[s][g] = lt.wrow[s][g] * bx[g];
+      for (int g = 0; g < KG; ++g) {
+        if constexpr (AS)
+          o[s][g] = bx[g];
+        else
+          o[s][g] = lt.wrow[s][g] * bx[g];
+      }
     }
   }
   if constexpr (XF) {
@@ -797,8 +811,9 @@ __device__ __attribute__((always_inline)) inline void mf_solve(
   for (int s = 0; s < F::SX; ++s) {
     const int l = 64 * s + lane;
     if (l < F::NLX) {
-      const int64_t row = e * N3 + (int64_t)l * N;  // row (j, k) = k * N + j = l
-      if constexpr (N % 4 == 0) {
+      // row (j, k) = k * NK + j = l
+      const int64_t row = e * (NK * NK * NK) + (int64_t)l * NK;
+      if constexpr (NK % 4 == 0) {
 #pragma unroll
         for (int g = 0; g < KG; ++g) *reinterpret_cast<mf4_t *>(z + row + 4 * g) = o[s][g];
       } else {
@@ -806,7 +821,7 @@ __device__ __attribute__((always_inline)) inline void mf_solve(
         for (int g = 0; g < KG; ++g)
 #pragma unroll
           for (int i = 0; i < 4; ++i)
-            if (4 * g + i < N) z[row + 4 * g + i] = o[s][g][i];
+            if (4 * g + i < NK) z[row + 4 * g + i] = o[s][g][i];
       }
     }
   }
@@ -817,7 +832,8 @@ __device__ __attribute__((always_inline)) inline void mf_solve(
 // grid and Dirichlet faces that give the RAS weight, z = output E-vector(s).  Each wavefront
 // solves C consecutive elements, loading the next element's inputs before it
 // solves the current one, so that the loads of one overlap the other's work.
-template <int P, int C, bool RS, int XS, bool YS, bool XF>
+// AS: additive Schwarz, z = the boxes.
+template <int P, int C, bool RS, int XS, bool YS, bool XF, bool AS = false>
 __global__ __launch_bounds__(256) void k_fdm_mf32(int64_t E, int nex, int ney, int nez,
                                                   const float *__restrict__ r,
                                                   const float *__restrict__ rs,
@@ -825,7 +841,7 @@ __global__ __launch_bounds__(256) void k_fdm_mf32(int64_t E, int nex, int ney, i
                                                   const float *__restrict__ lamg,
                                                   RasW W,
                                                   float *__restrict__ z, int nv) {
-  using F = Mf<P>;
+  using F = Mf<P, AS>;
   constexpr int N3 = F::N3;
   static_assert(!XF || C == 1, "x-face sums: one element per wave");
   __shared__ mf4_t lds4[F::WAVES * F::BUF / 4];
@@ -839,7 +855,7 @@ __global__ __launch_bounds__(256) void k_fdm_mf32(int64_t E, int nex, int ney, i
   if (e0 >= E) return;
   r += (int64_t)vec * E * N3;
   if (RS) rs += (int64_t)vec * E * N3;
-  z += (int64_t)vec * E * N3;
+  z += (int64_t)vec * E * (F::NK * F::NK * F::NK);
   float *buf = reinterpret_cast<float *>(lds4) + wave * F::BUF;
   // the wave reads r (and rs) only between a plane and a line below its first
   // element and as far above its last: one buffer window from there, whose
@@ -848,16 +864,16 @@ __global__ __launch_bounds__(256) void k_fdm_mf32(int64_t E, int nex, int ney, i
   const int64_t wb = (E - eb) * N3 * 4;
   const uint32_t wn = wb < (int64_t)kWindowMax ? (uint32_t)wb : kWindowMax;
   const BufF32 rb(r + eb * N3, wn), rsb(RS ? rs + eb * N3 : r + eb * N3, wn);
-  MfIn<P, RS, XS, YS> in[2];
-  mf_load<P, RS, XS, YS>(in[0], e0, nex, ney, nez, rb, rsb, eb, Sg, lamg, W, lane);
+  MfIn<P, RS, XS, YS, AS> in[2];
+  mf_load<P, RS, XS, YS, kOpF32, AS>(in[0], e0, nex, ney, nez, rb, rsb, eb, Sg, lamg, W, lane);
 #pragma unroll
   for (int it = 0; it < C; ++it) {
     const int64_t e = e0 + it;
     if (e >= E) break;
     if (it + 1 < C)  // (past the last element: reloads it, unused)
-      mf_load<P, RS, XS, YS>(in[(it + 1) & 1], e + 1 < E ? e + 1 : e, nex, ney, nez, rb, rsb, eb, Sg,
+      mf_load<P, RS, XS, YS, kOpF32, AS>(in[(it + 1) & 1], e + 1 < E ? e + 1 : e, nex, ney, nez, rb, rsb, eb, Sg,
                          lamg, W, lane);
-    mf_solve<P, RS, XS, YS, XF>(in[it & 1], e, lamg, z, buf, lane, xfx, wave, Sg, W);
+    mf_solve<P, RS, XS, YS, XF, kOpF32, AS>(in[it & 1], e, lamg, z, buf, lane, xfx, wave, Sg, W);
   }
 }
 
@@ -933,6 +949,33 @@ void mf32_launch_x(const Ctx &c, const Level &L, const float *r, const float *rs
     }
     SEM_LAUNCH("k_fdm_mf32");
   }
+}
+
+// additive Schwarz: z = the boxes [E][pb^3] of one right side; xin without the
+// x-face sums
+template <int P>
+void mf32_launch_asm(const Ctx &c, const Level &L, const float *r, const float *rs, float *z,
+                     hipStream_t s, int xin) {
+  using F = Mf<P, true>;
+  const int which = xin & 3;
+  const bool ys = (xin & 4) != 0;
+  if (xin & ~7 || which == 3 || (ys && which == 0) || (which == 1 && rs) || (which == 2 && !rs))
+    fail(SEM_EINVAL, "FDM: unknown form of the deferred gather-scatter steps");
+  const dim3 grid((unsigned)((L.E + F::WAVES - 1) / F::WAVES)), block(64 * F::WAVES);
+#define SEM_ASM_LAUNCH(RS, XS, YS)                                                               \
+  hipLaunchKernelGGL((k_fdm_mf32<P, 1, RS, XS, YS, false, true>), grid, block, 0, s, L.E, c.nex, \
+                     c.ney, c.nez, r, rs, L.S32, L.lam32, ras_w(L), z, 1)
+  if (rs) {
+    if (which == 2 && ys) SEM_ASM_LAUNCH(true, 2, true);
+    else if (which == 2) SEM_ASM_LAUNCH(true, 2, false);
+    else SEM_ASM_LAUNCH(true, 0, false);
+  } else {
+    if (which == 1 && ys) SEM_ASM_LAUNCH(false, 1, true);
+    else if (which == 1) SEM_ASM_LAUNCH(false, 1, false);
+    else SEM_ASM_LAUNCH(false, 0, false);
+  }
+#undef SEM_ASM_LAUNCH
+  SEM_LAUNCH("k_fdm_mf32");
 }
 
 // xin: 0 the inputs are assembled; 1 r, 2 rs lacks the x step of its
@@ -1036,6 +1079,11 @@ bool fdm_mf32_supported(const Ctx &c, int p) {
   return p >= 2 && p <= 9 && !floating && span * (p + 1) * (p + 1) * (p + 1) * 4 < kWindowMax;
 }
 
+// ASM at p = 2 stays with the vector kernel (seven boxes per workgroup there;
+// 85184 elements with the overlap sum: 78 us against 90 us on the matrix cores,
+// at p = 3, 32768 elements, 43 against 41 us, at p = 7, 4096, 32 against 27).
+bool fdm_mf32_asm_supported(const Ctx &c, int p) { return p >= 3 && fdm_mf32_supported(c, p); }
+
 template <int OP>
 static void mf_launch_p(const Ctx &c, const Level &L, const float *r, float *z, hipStream_t s,
                         int nv, const float *rs, int xin) {
@@ -1061,6 +1109,21 @@ void launch_fdm_mf32(const Ctx &c, const Level &L, const float *r, float *z, hip
     mf_launch_p<kOpBF16>(c, L, r, z, s, nv, rs, xin);
   else
     mf_launch_p<kOpF32>(c, L, r, z, s, nv, rs, xin);
+}
+
+void launch_fdm_mf32_asm(const Ctx &c, const Level &L, const float *r, float *box, hipStream_t s,
+                         const float *rs, int xin) {
+  if (!L.S32 || !L.lam32) fail(SEM_EINVAL, "FP32 FDM data were not built");
+  switch (L.p) {
+    case 3: mf32_launch_asm<3>(c, L, r, rs, box, s, xin); break;
+    case 4: mf32_launch_asm<4>(c, L, r, rs, box, s, xin); break;
+    case 5: mf32_launch_asm<5>(c, L, r, rs, box, s, xin); break;
+    case 6: mf32_launch_asm<6>(c, L, r, rs, box, s, xin); break;
+    case 7: mf32_launch_asm<7>(c, L, r, rs, box, s, xin); break;
+    case 8: mf32_launch_asm<8>(c, L, r, rs, box, s, xin); break;
+    case 9: mf32_launch_asm<9>(c, L, r, rs, box, s, xin); break;
+    default: fail(SEM_EUNSUPPORTED, "matrix-core FDM: unsupported degree");
+  }
 }
 
 }  // namespace sem

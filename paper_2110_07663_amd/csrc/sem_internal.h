@@ -422,6 +422,10 @@ bool fdm_mf32_supported(const Ctx &c, int p);
 // SEM_BF16 with the level's 16-bit factors)
 void launch_fdm_mf32(const Ctx &c, const Level &L, const float *r, float *z, hipStream_t s, int nv,
                      const float *rs, int xin, int prec = SEM_F32);
+bool fdm_mf32_asm_supported(const Ctx &c, int p);
+// FP32 ASM: box = the whole boxes [E][pb^3] of one right side
+void launch_fdm_mf32_asm(const Ctx &c, const Level &L, const float *r, float *box, hipStream_t s,
+                         const float *rs, int xin);
 // 32-bit words per element of L.A16 (degree p, 2 <= p <= 9), and its setup
 // from L.S16
 size_t mf16_table_words(int p);

@@ -501,14 +501,17 @@ static void opA_dot(const Ctx &c, const Level &L, const double *p, double *q, do
 // of the gather-scatter may be left to that update (xd->on says so)
 // Whether the level's Schwarz smoother in precision T reads A's output with
 // the x step of its gather-scatter left out and takes that step itself (the
-// FP32 matrix-core RAS kernel); then the products that only feed it skip it.
-// Whether the level's RAS local solves run in the matrix-core line kernel
-// (fdm_mf32.hip): FP32 operands, or FP16 / BF16 operands in its 4x4x4 form
-// (otherwise the 16-bit tile kernel of fdm_mfma.hip)
+// FP32 matrix-core kernel); then the products that only feed it skip it.
+// Whether the level's local solves run in the matrix-core line kernel
+// (fdm_mf32.hip): FP32 operands (RAS or ASM), or for RAS FP16 / BF16 operands in
+// its 4x4x4 form (otherwise the 16-bit tile kernel of fdm_mfma.hip)
 static bool fdm_in_mf(const Ctx &c, const Level &L) {
   const bool b16 = c.fdm_prec == SEM_BF16 || c.fdm_prec == SEM_F16;
-  return (b16 ? c.fdm_mf16 && L.A16 && L.sscale : c.fdm_mf32) &&
-         c.opts.smoother == SEM_SMOOTH_RAS && !L.coarse && fdm_mf32_supported(c, L.p);
+  const bool ras = c.opts.smoother == SEM_SMOOTH_RAS;
+  return (b16 ? c.fdm_mf16 && L.A16 && L.sscale && ras : c.fdm_mf32) &&
+         !L.coarse &&
+         (ras ? fdm_mf32_supported(c, L.p)
+              : c.opts.smoother == SEM_SMOOTH_ASM && fdm_mf32_asm_supported(c, L.p));
 }
 
 template <typename T>
@@ -527,7 +530,8 @@ static bool fdm_takes_y_step(const Ctx &c, const Level &L) {
 // shares (four consecutive elements along x) before it stores
 template <typename T>
 static bool fdm_sums_x_faces(const Ctx &c, const Level &L) {
-  return sizeof(T) == 4 && c.fdm_xfaces && fdm_in_mf(c, L) && L.gs_struct && L.nex % 4 == 0 &&
+  return sizeof(T) == 4 && c.fdm_xfaces && c.opts.smoother == SEM_SMOOTH_RAS && fdm_in_mf(c, L) &&
+         L.gs_struct && L.nex % 4 == 0 &&
          L.E % 4 == 0;
 }
 
@@ -555,7 +559,7 @@ static void opS(const Ctx &c, const Level &L, const T *r, T *z, hipStream_t s, i
   const bool mf16 = b16 && !asm_mode && fdm_in_mf(c, L);  // 16-bit line kernel
   const bool mfma = b16 && !mf16;                         // 16-bit tile kernel
   if (xin && !fdm_takes_x_step<T>(c, L)) fail(SEM_EINVAL, "smoother: inputs must be assembled");
-  if (rs && (!schwarz || asm_mode || mfma)) {  // form r - rs in rs, then apply S to it
+  if (rs && (!schwarz || mfma)) {  // form r - rs in rs, then apply S to it
     launch_sub<T>(L.nloc * nv, r, rs, rs, s);
     r = rs;
     rs = nullptr;
