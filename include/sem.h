@@ -99,7 +99,8 @@ typedef struct {
   double coarse_tol;          /* relative residual of the coarse Jacobi-PCG; 0 = run      */
   int32_t coarse_maxit;       /*   exactly coarse_maxit iterations                        */
   int32_t ax_variant;         /* Ax kernel shape at p = 7: 0 generic slab kernel, 1 one   */
-                              /* wavefront per element, 2 same with non-temporal streams, */
+                              /* wavefront per element, 2 same with non-temporal streams */
+                              /* where a level exceeds the last-level cache,           */
                               /* -1 library default                                       */
   int32_t batch_rhs;          /* right sides this context can take in sem_batch_solve     */
   int32_t coarse_solver;      /* p = 1 coarsest level: 0 Jacobi-PCG (coarse_tol,          */

@@ -163,7 +163,7 @@ __global__ __launch_bounds__(AxShape<N>::BS) void k_ax(int64_t E, const T *__res
 // t-line of u and of the output (registers).  Plane exchanges are within one
 // wavefront: LDS operations of a wavefront complete in issue order, and the
 // wave barriers keep the compiler from moving LDS accesses across phases.
-// streaming loads/stores: NT = true marks them non-temporal (no reuse)
+// NT, NTS = true: loads, stores marked non-temporal (no reuse)
 template <bool NT, typename T>
 __device__ __forceinline__ T ld(const T *p) {
   if constexpr (NT) return __builtin_nontemporal_load(p);
@@ -191,7 +191,7 @@ __device__ __forceinline__ void st(T *p, T v) {
 // GH (FP32 only): the factors come as FP16 pairs from G16, and the element's
 // result is multiplied by gsc[e] before the x-face sums and the store.
 
-template <typename T, bool NT, bool XF, bool GH = false>
+template <typename T, bool NT, bool NTS, bool XF, bool GH = false>
 __device__ __forceinline__ void ax8_body(int64_t E, const T *__restrict__ u,
                                          const T *__restrict__ G, const T *__restrict__ Dg,
                                          T *__restrict__ v, int nv, T *sD, T (*sU)[72],
@@ -299,58 +299,65 @@ __device__ __forceinline__ void ax8_body(int64_t E, const T *__restrict__ u,
   }
   T *ve = v + e * N3 + lane;
 #pragma unroll
-  for (int k = 0; k < N; ++k) st<NT>(ve + k * NN, acc[k]);
+  for (int k = 0; k < N; ++k) st<NTS>(ve + k * NN, acc[k]);
 }
 
 // register budgets: FP64 at 4 waves/SIMD, FP32 at 6
-template <bool NT, bool XF>
+template <bool NT, bool NTS, bool XF>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_ax8_f64(
     int64_t E, const double *__restrict__ u, const double *__restrict__ G,
     const double *__restrict__ Dg, double *__restrict__ v, int nv, double *dotp) {
   __shared__ double sD[64], sU[4][72], sR[4][72], sS[4][72];
-  ax8_body<double, NT, XF>(E, u, G, Dg, v, nv, sD, sU, sR, sS, dotp);
+  ax8_body<double, NT, NTS, XF>(E, u, G, Dg, v, nv, sD, sU, sR, sS, dotp);
 }
-template <bool NT, bool XF>
+template <bool NT, bool NTS, bool XF>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) void k_ax8_f32(
     int64_t E, const float *__restrict__ u, const float *__restrict__ G,
     const float *__restrict__ Dg, float *__restrict__ v, int nv) {
   __shared__ float sD[64], sU[4][72], sR[4][72], sS[4][72];
-  ax8_body<float, NT, XF>(E, u, G, Dg, v, nv, sD, sU, sR, sS);
+  ax8_body<float, NT, NTS, XF>(E, u, G, Dg, v, nv, sD, sU, sR, sS);
 }
 
-template <bool NT, bool XF>
+template <bool NT, bool NTS, bool XF>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) void k_ax8_f32h(
     int64_t E, const float *__restrict__ u, const uint32_t *__restrict__ G16,
     const float *__restrict__ gsc, const float *__restrict__ Dg, float *__restrict__ v, int nv) {
   __shared__ float sD[64], sU[4][72], sR[4][72], sS[4][72];
-  ax8_body<float, NT, XF, true>(E, u, nullptr, Dg, v, nv, sD, sU, sR, sS, nullptr, G16, gsc);
+  ax8_body<float, NT, NTS, XF, true>(E, u, nullptr, Dg, v, nv, sD, sU, sR, sS, nullptr, G16, gsc);
 }
 
 template <typename T, bool XF>
 static void ax8_launch(const Level &L, const T *u, T *v, const T *G, const T *D, int nv,
                        hipStream_t s, double *dotp) {
-  // several right sides share G through L2: plain loads (non-temporal ones would bypass it)
+  // Several right sides share G through L2: plain loads (non-temporal ones would
+  // bypass it).  One right side streams G, u and v past the caches only where
+  // they do not fit: the last-level cache holds 256 MB, and a level whose product
+  // reads and writes less (u, v, G: 8 words per point, 5 with FP16 factors) finds
+  // G there in the next one.  Cheby-RAS(2) smoothing at p = 7, plain against
+  // non-temporal loads: 8^3 elements FP64 85 / 91 us, FP32 62 / 67, 12^3 124 / 133
+  // and 79 / 86, 16^3 (134 MB in FP64) 211 / 231, 20^3 (131 MB in FP32) 187 / 206;
+  // 20^3 in FP64 (262 MB) 429 / 401, 24^3 in FP64 727 / 657.
+  // v is read next by the gather-scatter: plain stores keep it in the last-level
+  // cache up to 100 MB (32^3, 67 MB in FP32: product 128 us against 133); at 134 MB
+  // (32^3 in FP64) they displace what the next call reads (255 us against 236).
+  constexpr double kLoadMB = 192.0, kStoreMB = 100.0;
   const dim3 grid((unsigned)((L.E + 3) / 4 * nv));
-  const bool nt = L.ax_variant == 2 && nv == 1;
+  const double mb = (double)L.nloc * sizeof(T) * 1e-6;
+  const bool stream = L.ax_variant == 2 && nv == 1;
+  const bool nt = stream && mb * (sizeof(T) == 4 && L.G16 ? 5 : 8) > kLoadMB;
+  const bool nts = stream && mb > kStoreMB;
+#define SEM_AX8(K, ...)                                                                       \
+  if (nt && nts) hipLaunchKernelGGL((K<true, true, XF>), grid, dim3(256), 0, s, __VA_ARGS__); \
+  else if (nt) hipLaunchKernelGGL((K<true, false, XF>), grid, dim3(256), 0, s, __VA_ARGS__);  \
+  else hipLaunchKernelGGL((K<false, false, XF>), grid, dim3(256), 0, s, __VA_ARGS__)
   if constexpr (sizeof(T) == 8) {
-    if (nt)
-      hipLaunchKernelGGL((k_ax8_f64<true, XF>), grid, dim3(256), 0, s, L.E, u, G, D, v, nv, dotp);
-    else
-      hipLaunchKernelGGL((k_ax8_f64<false, XF>), grid, dim3(256), 0, s, L.E, u, G, D, v, nv,
-                         dotp);
+    SEM_AX8(k_ax8_f64, L.E, u, G, D, v, nv, dotp);
   } else if (L.G16) {  // FP16 factors
-    if (nt)
-      hipLaunchKernelGGL((k_ax8_f32h<true, XF>), grid, dim3(256), 0, s, L.E, u, L.G16, L.gscale,
-                         D, v, nv);
-    else
-      hipLaunchKernelGGL((k_ax8_f32h<false, XF>), grid, dim3(256), 0, s, L.E, u, L.G16, L.gscale,
-                         D, v, nv);
+    SEM_AX8(k_ax8_f32h, L.E, u, L.G16, L.gscale, D, v, nv);
   } else {
-    if (nt)
-      hipLaunchKernelGGL((k_ax8_f32<true, XF>), grid, dim3(256), 0, s, L.E, u, G, D, v, nv);
-    else
-      hipLaunchKernelGGL((k_ax8_f32<false, XF>), grid, dim3(256), 0, s, L.E, u, G, D, v, nv);
+    SEM_AX8(k_ax8_f32, L.E, u, G, D, v, nv);
   }
+#undef SEM_AX8
   SEM_LAUNCH("k_ax8");
 }
 
