@@ -389,8 +389,9 @@ static void ax_n(const Level &L, const T *u, T *v, const T *G, const T *D, int n
   SEM_LAUNCH("k_ax");
 }
 
-bool ax_sums_x_faces(const Level &L) {
-  return L.gs_struct && L.xfuse && L.N == 8 && L.ax_variant >= 1 && L.nex % 4 == 0;
+bool ax_sums_x_faces(const Level &L, size_t word, int nv) {
+  return L.gs_struct && L.xfuse && L.N == 8 && L.ax_variant >= 1 && L.nex % 4 == 0 &&
+         !gs_in_one_launch(L, word, nv);
 }
 
 bool ax_forms_dot(const Level &L, int nv) { return L.N == 8 && L.ax_variant >= 1 && nv == 1; }
@@ -398,7 +399,7 @@ bool ax_forms_dot(const Level &L, int nv) { return L.N == 8 && L.ax_variant >= 1
 template <typename T>
 void launch_ax(const Level &L, const T *u, T *v, hipStream_t s, int nv, bool xf, double *dotp) {
   if (nv < 1) fail(SEM_EINVAL, "Ax: no right side");
-  if (xf && !ax_sums_x_faces(L)) fail(SEM_EINVAL, "Ax: x-face summation not available here");
+  if (xf && !ax_sums_x_faces(L, sizeof(T), nv)) fail(SEM_EINVAL, "Ax: x-face summation not available here");
   if (dotp && (sizeof(T) != 8 || !ax_forms_dot(L, nv)))
     fail(SEM_EINVAL, "Ax: the element shares of (u, Au) need the FP64 p = 7 one-wave kernel");
   const T *G;

@@ -466,6 +466,99 @@ __global__ void k_gs_yz(T *__restrict__ v, GsGrid g, int64_t E, int64_t ny_t, in
       if (idx[zs][ys] >= 0) v[idx[zs][ys]] = tot;
 }
 
+// All three passes in one launch, with the same sums in the same order: every
+// node on an element boundary belongs to one thread, which reads its up to 8
+// copies, takes the x, then the y, then the z step and writes the total to all of
+// them.  The nodes come in seven sets by the directions they are shared in (bit
+// 0: x, 1: y, 2: z): along a shared direction a node is a face of the element
+// grid (0..n), along another an element and an interior node (1..p-1).
+//
+// For levels whose passes are launches and little else: apply_A with three
+// launches against this one, FP64 / FP32: p = 3, 5^3 elements 13.1 / 9.2 and
+// 15.7 / 9.2 us; p = 7, 9^3 (104,000 boundary nodes) 14.4 / 14.8 and 15.6 / 11.0;
+// p = 9, 9^3 (178,000) 21.8 / 21.1 and 17.8 / 15.1.  Above, the sets reach the
+// same lines from different XCDs, and the passes, which walk the elements in
+// order, are faster: p = 7, 13^3 (304,000) 25.5 / 27.0 and 17.8 / 19.0.
+constexpr int64_t kGsAll64 = 120000, kGsAll32 = 180000;  // boundary nodes times right sides
+struct GsSets {
+  unsigned end[7];  // cumulative thread counts of the sets 1..7
+};
+template <typename T>
+__global__ __launch_bounds__(256) void k_gs_all(T *__restrict__ v, GsGrid g, int64_t E, GsSets S) {
+  unsigned t = xcd_block() * blockDim.x + threadIdx.x;
+  if (t >= S.end[6]) return;
+  const unsigned p = (unsigned)g.p, N = (unsigned)g.N, q = p - 1;
+  v += blockIdx.y * E * ((int64_t)N * N * N);  // right side blockIdx.y
+  int set = 1;
+  unsigned from = 0;
+#pragma unroll
+  for (int m = 0; m < 6; ++m)
+    if (t >= S.end[m]) {
+      set = m + 2;
+      from = S.end[m];
+    }
+  t -= from;
+  const unsigned n[3] = {(unsigned)g.nex, (unsigned)g.ney, (unsigned)g.nez};
+  unsigned off[3][2];  // element index of the two sides times the direction's stride, + node
+  bool has[3][2];
+  bool zero = false;
+  const unsigned es[3] = {1u, n[0], n[0] * n[1]}, ns[3] = {1u, N, N * N};
+  const unsigned N3 = N * N * N;
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    const bool sh = (set >> d) & 1;
+    const unsigned cnt = sh ? n[d] + 1 : n[d] * q;
+    const unsigned c = d < 2 ? t % cnt : t;
+    if (d < 2) t /= cnt;
+    if (sh) {
+      has[d][0] = c > 0;
+      has[d][1] = c < n[d];
+      off[d][0] = (c - 1) * es[d] * N3 + p * ns[d];
+      off[d][1] = c * es[d] * N3;
+      zero = zero || (c == 0 && g.bc[2 * d]) || (c == n[d] && g.bc[2 * d + 1]);
+    } else {
+      const unsigned e = c / q, m = 1 + c - e * q;
+      has[d][0] = true;
+      has[d][1] = false;
+      off[d][0] = e * es[d] * N3 + m * ns[d];
+      off[d][1] = 0;
+    }
+  }
+  // (nloc < 2^31: 32-bit indices)
+  T tot = T(0), val[2][2][2];
+#pragma unroll
+  for (int z = 0; z < 2; ++z)
+#pragma unroll
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+      for (int x = 0; x < 2; ++x)
+        val[z][y][x] = has[0][x] && has[1][y] && has[2][z] ? v[off[0][x] + off[1][y] + off[2][z]] : T(0);
+  if (!zero)
+    tot = ((val[0][0][0] + val[0][0][1]) + (val[0][1][0] + val[0][1][1])) +
+          ((val[1][0][0] + val[1][0][1]) + (val[1][1][0] + val[1][1][1]));
+#pragma unroll
+  for (int z = 0; z < 2; ++z)
+#pragma unroll
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+      for (int x = 0; x < 2; ++x)
+        if (has[0][x] && has[1][y] && has[2][z]) v[off[0][x] + off[1][y] + off[2][z]] = tot;
+}
+
+static int64_t gs_set_nodes(const Level &L, int set) {
+  const int64_t n[3] = {L.nex, L.ney, L.nez};
+  int64_t cnt = 1;
+  for (int d = 0; d < 3; ++d) cnt *= (set >> d) & 1 ? n[d] + 1 : n[d] * (L.p - 1);
+  return cnt;
+}
+bool gs_in_one_launch(const Level &L, size_t word, int nv) {
+  if (!L.gs_struct || L.gs_all == 0) return false;
+  int64_t total = 0;
+  for (int m = 1; m < 8; ++m) total += gs_set_nodes(L, m);
+  if (L.gs_all == 1) return total * nv < ((int64_t)1 << 31);
+  return total * nv <= (word == 8 ? kGsAll64 : kGsAll32);
+}
+
 template <typename T>
 void launch_gs(const Level &L, T *v, hipStream_t s, int nv, bool x_in_blocks, bool skip_x,
                bool skip_y) {
@@ -478,6 +571,18 @@ void launch_gs(const Level &L, T *v, hipStream_t s, int nv, bool x_in_blocks, bo
     g.nex = L.nex; g.ney = L.ney; g.nez = L.nez; g.p = L.p; g.N = L.N;
     for (int f = 0; f < 6; ++f) g.bc[f] = L.bc[f];
     const dim3 grid(nb(L.E * L.N * L.N, 256), (unsigned)nv);
+    if (!skip_x && !skip_y && !x_in_blocks && gs_in_one_launch(L, sizeof(T), nv)) {
+      GsSets S;
+      int64_t total = 0;
+      for (int m = 1; m < 8; ++m) {
+        total += gs_set_nodes(L, m);
+        S.end[m - 1] = (unsigned)total;
+      }
+      hipLaunchKernelGGL((k_gs_all<T>), dim3(nb(total, 256), (unsigned)nv), dim3(256), 0, s, v, g,
+                         L.E, S);
+      SEM_LAUNCH("k_gs_all");
+      return;
+    }
     if (skip_x) {
       // the consumer takes the x step (the passes commute up to rounding)
     } else if (x_in_blocks) {

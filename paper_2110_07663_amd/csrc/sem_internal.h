@@ -109,6 +109,7 @@ struct Level {
   bool gs_struct = true;             // false: the sorted-numbering segments (perm/off)
   bool xfuse = true;                 // the p = 7 Ax sums x-faces inside its workgroups
   int gs_yz = -1;                    // y and z passes in one launch: 1 yes, 0 no, -1 FP64 only
+  int gs_all = -1;                   // all passes in one launch: 1 yes, 0 no, -1 small levels only
   bool xdefer = true;                // Chebyshev updates may take the x step of S's gather-scatter
   bool ydefer = true;                // ... and its y step
   double *dotpart = nullptr;         // [E] element shares of (p, Ap) (finest level)
@@ -302,6 +303,9 @@ void launch_gather(const Ctx &c, const Level &L, const double *ug, double *ul, h
 template <typename T>
 void launch_gs(const Level &L, T *v, hipStream_t s, int nv = 1, bool x_in_blocks = false,
                bool skip_x = false, bool skip_y = false);  // skip: leave that pass out
+// whether launch_gs takes all passes of this level in one launch (nv vectors of
+// word bytes); a producer then leaves the x-faces inside its workgroups to it
+bool gs_in_one_launch(const Level &L, size_t word, int nv);
 void launch_weights(const Level &L, hipStream_t s);
 void launch_start_vector(const Ctx &c, const Level &L, uint64_t seed, double *v, hipStream_t s);
 
@@ -315,7 +319,7 @@ void launch_ax(const Level &L, const T *u, T *v, hipStream_t s, int nv = 1, bool
 bool ax_forms_dot(const Level &L, int nv);
 // out = sum of part[0..n) in a fixed order
 void launch_sum_partials(int64_t n, const double *part, double *out, hipStream_t s);
-bool ax_sums_x_faces(const Level &L);
+bool ax_sums_x_faces(const Level &L, size_t word, int nv);
 void launch_diag(const Level &L, double *d, hipStream_t s);
 
 // blas.hip

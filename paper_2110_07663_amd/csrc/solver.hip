@@ -339,6 +339,11 @@ static void init_ctx(Ctx &c, const sem_mesh *m, int p, const int8_t *bc, const s
       // and slower in FP32)
       const char *yzv = getenv("SEM_GS_YZ");
       L.gs_yz = yzv ? (yzv[0] == '1' ? 1 : 0) : -1;
+      // SEM_GS_ALL=0 / 1: separate passes / one launch for all of them on every
+      // level (default: one launch on small levels, unless SEM_GS_YZ asks for
+      // a form of the passes)
+      const char *gav = getenv("SEM_GS_ALL");
+      L.gs_all = gav ? (gav[0] == '1' ? 1 : 0) : (yzv ? 0 : -1);
     }
     L.lowp = c.lowp;
     // Ax kernel shape at p = 7 (option, else SEM_AX_VARIANT, else one wave/element,
@@ -445,7 +450,7 @@ struct ProfScope {
 template <typename T>
 static void opA(const Ctx &c, const Level &L, const T *u, T *Au, hipStream_t s, int nv = 1,
                 double *dotp = nullptr) {
-  const bool xf = ax_sums_x_faces(L);  // Ax sums the x-faces inside its workgroups
+  const bool xf = ax_sums_x_faces(L, sizeof(T), nv);  // Ax sums the x-faces inside its workgroups
   {
     ProfScope ps(c, L, sizeof(T) == 8 ? SEM_PROF_AX64 : SEM_PROF_AX32, s);
     launch_ax<T>(L, u, Au, s, nv, xf, dotp);
@@ -529,9 +534,9 @@ static bool fdm_takes_y_step(const Ctx &c, const Level &L) {
 // Whether the FP32 matrix-core RAS kernel sums the x-faces its workgroup
 // shares (four consecutive elements along x) before it stores
 template <typename T>
-static bool fdm_sums_x_faces(const Ctx &c, const Level &L) {
+static bool fdm_sums_x_faces(const Ctx &c, const Level &L, int nv) {
   return sizeof(T) == 4 && c.fdm_xfaces && c.opts.smoother == SEM_SMOOTH_RAS && fdm_in_mf(c, L) &&
-         L.gs_struct && L.nex % 4 == 0 &&
+         L.gs_struct && !gs_in_one_launch(L, sizeof(T), nv) && L.nex % 4 == 0 &&
          L.E % 4 == 0;
 }
 
@@ -574,7 +579,7 @@ static void opS(const Ctx &c, const Level &L, const T *r, T *z, hipStream_t s, i
   // or arrive with the x-faces inside each FDM workgroup summed
   const bool defer = !asm_mode && xd && L.gs_struct && L.xdefer &&
                      cheb_can_defer_x<T>(L.N, L.nloc * nv, {z});
-  const bool fxf = !asm_mode && !defer && !mfma && (xin & 3) != 1 && fdm_sums_x_faces<T>(c, L);
+  const bool fxf = !asm_mode && !defer && !mfma && (xin & 3) != 1 && fdm_sums_x_faces<T>(c, L, nv);
   {
     ProfScope ps(c, L, SEM_PROF_FDM, s);
     if constexpr (sizeof(T) == 4) {
