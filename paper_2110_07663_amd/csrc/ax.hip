@@ -57,6 +57,13 @@ __global__ __launch_bounds__(AxShape<N>::BS) void k_ax(int64_t E, const T *__res
                                                        const float *__restrict__ gsc) {
   using S = AxShape<N>;
   constexpr int NN = S::NN, N3 = S::N3, EPB = S::EPB, RS = S::RS, PS = S::PS;
+  // k-planes of G requested together with u, before the first barrier, so that
+  // G arrives while the r and s derivatives run (the rest is requested where it
+  // is used).  With the gather-scatter, 4e6 nodes, FP32 / FP64, none against a
+  // quarter of the planes: p = 6 45.1 / 44.0 and 83.4 / 79.9 us, p = 8 55.7 / 52.8
+  // and 110 / 103, p = 9 48.2 / 43.6 and 74.9 / 69.6; more planes cost registers
+  // (p = 9 with all: 45.3 and 76.4); no gain below p = 5, nor at p = 10 in FP64.
+  constexpr int PF = N >= 6 && !(N == 11 && sizeof(T) == 8) ? (N + 3) / 4 : 0;
   __shared__ T sD[NN];
   __shared__ T s_a[EPB][N * PS];
   __shared__ T s_b[EPB][N * PS];
@@ -75,10 +82,24 @@ __global__ __launch_bounds__(AxShape<N>::BS) void k_ax(int64_t E, const T *__res
 
   // phase 1: the element's u into registers (t-lines) and LDS (planes)
   T uk[N];
+  T gk[N][GH ? 1 : 6];
+  uint32_t hk[N][GH ? 3 : 1];
+  const T *Ge = GH ? nullptr : G + e * 6 * N3 + ij;
+  const uint32_t *He = GH ? G16 + e * 3 * N3 + ij : nullptr;
   if (active) {
     const T *ue = u + e * N3 + ij;
 #pragma unroll
     for (int k = 0; k < N; ++k) uk[k] = ue[k * NN];
+#pragma unroll
+    for (int k = 0; k < PF; ++k) {
+      if constexpr (GH) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) hk[k][c] = He[c * N3 + k * NN];
+      } else {
+#pragma unroll
+        for (int c = 0; c < 6; ++c) gk[k][c] = Ge[c * N3 + k * NN];
+      }
+    }
 #pragma unroll
     for (int k = 0; k < N; ++k) s_a[le][k * PS + j * RS + i] = uk[k];
   }
@@ -109,8 +130,6 @@ __global__ __launch_bounds__(AxShape<N>::BS) void k_ax(int64_t E, const T *__res
   // phase 3: t derivative in registers, h = G g; h_r, h_s to LDS, h_t stays
   T wt[N];
   if (active) {
-    const T *Ge = GH ? nullptr : G + e * 6 * N3 + ij;
-    const uint32_t *He = GH ? G16 + e * 3 * N3 + ij : nullptr;
 #pragma unroll
     for (int k = 0; k < N; ++k) {
       T ut = 0;
@@ -118,14 +137,20 @@ __global__ __launch_bounds__(AxShape<N>::BS) void k_ax(int64_t E, const T *__res
       for (int l = 0; l < N; ++l) ut += sD[k * N + l] * uk[l];
       T g0, g1, g2, g3, g4, g5;
       if constexpr (GH) {
-        const uint32_t h01 = He[0 * N3 + k * NN], h23 = He[1 * N3 + k * NN];
-        const uint32_t h45 = He[2 * N3 + k * NN];
+        const uint32_t h01 = k < PF ? hk[k][0] : He[0 * N3 + k * NN];
+        const uint32_t h23 = k < PF ? hk[k][1] : He[1 * N3 + k * NN];
+        const uint32_t h45 = k < PF ? hk[k][2] : He[2 * N3 + k * NN];
         g0 = half_lo(h01); g1 = half_hi(h01);
         g2 = half_lo(h23); g3 = half_hi(h23);
         g4 = half_lo(h45); g5 = half_hi(h45);
       } else {
-        g0 = Ge[0 * N3 + k * NN]; g1 = Ge[1 * N3 + k * NN]; g2 = Ge[2 * N3 + k * NN];
-        g3 = Ge[3 * N3 + k * NN]; g4 = Ge[4 * N3 + k * NN]; g5 = Ge[5 * N3 + k * NN];
+        if (k < PF) {
+          g0 = gk[k][0]; g1 = gk[k][1]; g2 = gk[k][2];
+          g3 = gk[k][3]; g4 = gk[k][4]; g5 = gk[k][5];
+        } else {
+          g0 = Ge[0 * N3 + k * NN]; g1 = Ge[1 * N3 + k * NN]; g2 = Ge[2 * N3 + k * NN];
+          g3 = Ge[3 * N3 + k * NN]; g4 = Ge[4 * N3 + k * NN]; g5 = Ge[5 * N3 + k * NN];
+        }
       }
       s_a[le][k * PS + j * RS + i] = g0 * ur[k] + g1 * us[k] + g2 * ut;
       s_b[le][k * PS + j * RS + i] = g1 * ur[k] + g3 * us[k] + g4 * ut;
