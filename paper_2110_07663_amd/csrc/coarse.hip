@@ -822,7 +822,7 @@ void coarse_solve_assembled(Ctx &c, Level &C, double tol, int maxit, hipStream_t
   if (S.direct) {  // exact: no iteration, no host interaction (also inside a recorded graph)
     CoarseGrid g = cgrid(c);
     launch_to_global(S, g, C.d_b, u, nv, s);
-    coarse_direct_apply(S, g.nx, g.ny, g.nz, S.b, S.x, s, nv);
+    coarse_direct_apply(S, S.b, S.x, s, nv);
     if (!c.capturing) c.last_coarse_iters = 0;
     launch_gather(c, C, S.x, c.cx, s, nv, S.n);
     return;

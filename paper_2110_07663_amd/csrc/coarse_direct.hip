@@ -2,17 +2,20 @@
 // coarsest level) for the assembled p = 1 operator.
 //
 // With nodes numbered plane by plane along z, the 27-point operator is block
-// tridiagonal: D_k couples the nodes of plane k among themselves, A_{k,k-1} and
-// A_{k,k+1} couple it to the planes below and above.  Block elimination runs
-// from both ends towards the middle plane c = K/2 (a "twisted" factorisation),
-// so the solve has two independent chains of half the length:
+// tridiagonal in blocks of one or more whole planes: D_k couples the nodes of
+// block k among themselves, A_{k,k-1} its first plane to the last plane of the
+// block below, A_{k,k+1} its last plane to the first of the block above.  Block
+// elimination runs from both ends towards the middle block c = B/2 (a "twisted"
+// factorisation), so the solve has two independent chains of half the length:
 //   below c:  T_0 = D_0,  H_k = A_{k,k-1} G_{k-1},  T_k = D_k - H_k A_{k-1,k};
-//   above c:  T_{K-1} = D_{K-1},  H_k = A_{k,k+1} G_{k+1},  T_k = D_k - H_k A_{k+1,k};
+//   above c:  T_{B-1} = D_{B-1},  H_k = A_{k,k+1} G_{k+1},  T_k = D_k - H_k A_{k+1,k};
 //   at c:     T_c = D_c - Hd_c A_{c-1,c} - Hu_c A_{c+1,c}   (both updates);
 //   G_k = T_k^{-1}, and J_k = H_{k+1}^T (below c) or H_{k-1}^T (above c).
-// Solve: y_0 = b_0, y_{K-1} = b_{K-1}, y_k = b_k - H_k y_{k-+1} walking inwards,
-// y_c = b_c - Hd_c y_{c-1} - Hu_c y_{c+1}, x_c = G_c y_c, then outwards
-// x_k = G_k y_k - J_k x_{k+-1}.  One launch advances both chains.
+// H_k has the rows of one plane only (the first of block k below c, the last
+// above), J_k its columns.  Solve: y_k = b_k - H_k y_{k-+1} walking inwards (the
+// other planes of y_k are those of b_k), y_c = b_c - Hd_c y_{c-1} - Hu_c y_{c+1},
+// x_c = G_c y_c, then outwards x_k = G_k y_k - J_k x_{k+-1}.  One launch advances
+// both chains.
 // Each T_k is symmetric positive definite (a Schur complement of an SPD
 // matrix), so it is inverted in place by blocked Gauss-Jordan elimination
 // without pivoting (32x32 blocks: invert the pivot block, scale its block row,
@@ -21,14 +24,16 @@
 // row's diagonal (a numerically singular level, e.g. all-Neumann) is reported
 // and the caller keeps the CG.
 //
-// Storage: G, H, J as K dense [Mp][Mp] FP64 blocks, Mp = nx*ny rounded up to
-// 32 (identity / zero padding); Hu_c sits in J's slot c.  A solve reads each
-// block once: 3 K Mp^2 * 8 bytes, in about K dependent matrix-vector launches
-// with no host interaction, so it can be recorded into a graph.  Under an FP32
-// smoother the sweeps read FP32 copies of the factored blocks instead (half the
-// bytes; vectors and sums stay FP64): the solve is then exact to about 1e-6,
-// below what the FP32 V-cycle around it resolves.
+// Storage: per block G [Mp][Mp], H [mp][Mp] and J [Mp][mp] in FP64, Mp = the
+// nodes of a block and mp = those of a plane rounded up to 32 (identity / zero
+// padding); Hu_c sits in J's slot c.  A solve reads each block once, in about B
+// dependent matrix-vector launches with no host interaction, so it can be
+// recorded into a graph.  Under an FP32 smoother the sweeps read FP32 copies of
+// the factored blocks instead (half the bytes; vectors and sums stay FP64): the
+// solve is then exact to about 1e-6, below what the FP32 V-cycle around it
+// resolves.
 #include <algorithm>
+#include <cstdlib>
 
 #include "sem_internal.h"
 
@@ -38,10 +43,37 @@ constexpr int kGB = 32;  // Gauss-Jordan block
 
 static inline int64_t padded(int64_t m) { return (m + kGB - 1) / kGB * kGB; }
 
-size_t coarse_direct_bytes(int64_t nx, int64_t ny, int64_t nz, bool f32) {
-  const int64_t Mp = padded(nx * ny);
-  return (size_t)(3 * nz * Mp * Mp + nx * ny * nz) * sizeof(double) +
-         (f32 ? (size_t)(3 * nz * Mp * Mp) * sizeof(float) : 0);
+// Planes per block.  With g planes the solve is a chain of K / g launches instead
+// of K and reads (g + 2) / 3 times the bytes, and the setup inverts blocks g
+// times the size (g^2 times the operations).  g has the smallest sum of: 3.5 us
+// per launch (its time before the first byte), the bytes at 4 TB/s (measured, per
+// launch), and the inversions at 9 TFLOP/s (measured) spread over 300 solves; the
+// blocks stay below 64 M entries (or 1.5 times those of single planes).  5^3
+// nodes: one launch instead of 5; 9^3: one instead of 9 (32 us of an FP64 V-cycle's
+// 412 at 9x7x8, p = 9: now 391); 17^3: 3 instead of 17; 33^3 keeps single planes
+// (pairs: 1.3 % of the 32^3 solve for 30 ms of setup).
+BtShape coarse_direct_shape(int64_t nx, int64_t ny, int64_t nz, bool f32) {
+  BtShape best{};
+  double best_us = 0.0;
+  const int64_t m = nx * ny, mp = padded(m), one = 3 * nz * mp * mp;
+  const int64_t most = std::max<int64_t>((int64_t)64 << 20, one + one / 2);
+  // SEM_COARSE_PLANES=g: that many planes per block
+  const char *gv = getenv("SEM_COARSE_PLANES");
+  const int64_t forced = gv ? std::min<int64_t>(std::max(atoi(gv), 1), nz) : 0;
+  for (int64_t g = 1; g <= nz; ++g) {
+    const int64_t B = (nz + g - 1) / g, Mp = padded(g * m), c = B / 2;
+    const int64_t entries = B * (Mp * Mp + 2 * mp * Mp);
+    if (forced ? g != forced : g > 1 && entries > most) continue;
+    const int64_t up = std::max<int64_t>(std::max(c - 1, B - 2 - c), 0);
+    const int64_t launches = B == 1 ? 1 : up + 2 + std::max(c, B - 1 - c);
+    const double us = 3.5 * launches + (double)entries * (f32 ? 4 : 8) / 4e6 +
+                      2.0 * B * Mp * Mp * (double)Mp / 9e6 / 300.0;
+    if (best.g == 0 || us < best_us) {
+      best_us = us;
+      best = BtShape{(int)m, (int)nz, (int)g, (int)B, (int)Mp, (int)mp};
+    }
+  }
+  return best;
 }
 
 // ---- setup kernels ----------------------------------------------------------
@@ -51,32 +83,36 @@ __device__ inline double st_at(const double *St, int64_t n, int64_t t, int dx, i
   return St[(int64_t)((dz + 1) * 9 + (dy + 1) * 3 + (dx + 1)) * n + t];
 }
 
-// H[i][l] = sum_a A_{k,k+dz}[i][a] G_{k+dz}[a][l], A_{k,k+dz}[i][a] = stencil of
-// row (k, i) towards node (k + dz, a), dz = -1 or +1
-__global__ void k_bt_H(int nx, int ny, int64_t n, int k, int Mp, const double *__restrict__ St,
-                       const double *__restrict__ Gp, double *__restrict__ H, int dz) {
+// H[i][l] = sum_a A_{k,k+dz}[i][a] G_{k+dz}[a][l] (a over the plane of the
+// neighbouring block next to this one: its rows from ra), dz = -1 or +1; plane =
+// the plane of block k that takes it, ml = nodes of the neighbouring block
+__global__ void k_bt_H(int nx, int ny, int64_t n, int plane, int ml, int mp, int Mp, int ra,
+                       const double *__restrict__ St, const double *__restrict__ Gp,
+                       double *__restrict__ H, int dz) {
   const int m = nx * ny;
   const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (e >= (int64_t)Mp * Mp) return;
+  if (e >= (int64_t)mp * Mp) return;
   const int i = (int)(e / Mp), l = (int)(e - (int64_t)i * Mp);
   double h = 0.0;
-  if (i < m && l < m) {
+  if (i < m && l < ml) {
     const int xi = i % nx, yi = i / nx;
-    const int64_t row = (int64_t)k * m + i;
+    const int64_t row = (int64_t)plane * m + i;
     for (int dy = -1; dy <= 1; ++dy)
       for (int dx = -1; dx <= 1; ++dx) {
         const int xa = xi + dx, ya = yi + dy;
         if (xa < 0 || xa >= nx || ya < 0 || ya >= ny) continue;
-        h += st_at(St, n, row, dx, dy, dz) * Gp[(int64_t)(ya * nx + xa) * Mp + l];
+        h += st_at(St, n, row, dx, dy, dz) * Gp[(int64_t)(ra + ya * nx + xa) * Mp + l];
       }
   }
   H[e] = h;
 }
 
-// T[i][j] = D_k[i][j] - sum_l H1[i][l] A_{k,k+dz1}[j][l] - sum_l H2[i][l] A_{k,k+dz2}[j][l]
-// (A_{k+dz,k} = A_{k,k+dz}^T; absent updates are null; padding: identity).  The
+// T[i][j] = D_k[i][j] - sum_l H1[i][l] A_{k,k-1}[j][l] (first plane)
+//                     - sum_l H2[i][l] A_{k,k+1}[j][l] (last plane)
+// (A_{k+dz,k} = A_{k,k+dz}^T; absent updates are null; padding: identity).  H1's
+// columns of the plane below start at c1, H2's of the plane above at 0.  The
 // diagonal is also kept in `diag` for the pivot test of the inversion.
-__device__ inline double bt_update(int nx, int ny, int64_t n, int64_t rowj, int xj, int yj, int Mp,
+__device__ inline double bt_update(int nx, int ny, int64_t n, int64_t rowj, int xj, int yj,
                                    const double *__restrict__ St, const double *__restrict__ Hi,
                                    int dz) {
   double v = 0.0;
@@ -89,25 +125,29 @@ __device__ inline double bt_update(int nx, int ny, int64_t n, int64_t rowj, int 
   return v;
 }
 
-__global__ void k_bt_T(int nx, int ny, int64_t n, int k, int Mp, const double *__restrict__ St,
-                       const double *__restrict__ H1, int dz1, const double *__restrict__ H2,
-                       int dz2, double *__restrict__ T, double *__restrict__ diag) {
-  const int m = nx * ny;
+__global__ void k_bt_T(int nx, int ny, int64_t n, int plane0, int np, int Mp,
+                       const double *__restrict__ St, const double *__restrict__ H1, int c1,
+                       const double *__restrict__ H2, double *__restrict__ T,
+                       double *__restrict__ diag) {
+  const int m = nx * ny, M = np * m;
   const int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (e >= (int64_t)Mp * Mp) return;
   const int i = (int)(e / Mp), j = (int)(e - (int64_t)i * Mp);
-  if (i >= m || j >= m) {
+  if (i >= M || j >= M) {
     T[e] = i == j ? 1.0 : 0.0;
     if (i == j) diag[i] = 1.0;
     return;
   }
-  const int xi = i % nx, yi = i / nx, xj = j % nx, yj = j / nx;
-  const int dx = xj - xi, dy = yj - yi;
+  const int pi = i / m, pj = j / m, ii = i - pi * m, jj = j - pj * m;
+  const int xi = ii % nx, yi = ii / nx, xj = jj % nx, yj = jj / nx;
+  const int dx = xj - xi, dy = yj - yi, dz = pj - pi;
   double v = 0.0;
-  if (dx >= -1 && dx <= 1 && dy >= -1 && dy <= 1) v = st_at(St, n, (int64_t)k * m + i, dx, dy, 0);
-  const int64_t rowj = (int64_t)k * m + j;
-  if (H1) v -= bt_update(nx, ny, n, rowj, xj, yj, Mp, St, H1 + (int64_t)i * Mp, dz1);
-  if (H2) v -= bt_update(nx, ny, n, rowj, xj, yj, Mp, St, H2 + (int64_t)i * Mp, dz2);
+  if (dx >= -1 && dx <= 1 && dy >= -1 && dy <= 1 && dz >= -1 && dz <= 1)
+    v = st_at(St, n, (int64_t)(plane0 + pi) * m + ii, dx, dy, dz);
+  const int64_t rowj = (int64_t)(plane0 + pj) * m + jj;
+  if (H1 && pi == 0 && pj == 0) v -= bt_update(nx, ny, n, rowj, xj, yj, St, H1 + (int64_t)ii * Mp + c1, -1);
+  if (H2 && pi == np - 1 && pj == np - 1)
+    v -= bt_update(nx, ny, n, rowj, xj, yj, St, H2 + (int64_t)ii * Mp, 1);
   T[e] = v;
   if (i == j) diag[i] = v;
 }
@@ -211,28 +251,36 @@ __global__ __launch_bounds__(256) void k_gj_col(double *A, int Mp, int Kb) {
   }
 }
 
-// J[i][a] = H[a][i]
-__global__ void k_bt_transpose(int Mp, const double *__restrict__ H, double *__restrict__ J) {
+// J[i][a] = H[a][i], H [mp][Mp], J [Mp][mp]
+__global__ void k_bt_transpose(int mp, int Mp, const double *__restrict__ H,
+                               double *__restrict__ J) {
   __shared__ double t[32][33];
   const int bx = blockIdx.x * 32, by = blockIdx.y * 32;
   const int tx = threadIdx.x % 32, ty = threadIdx.x / 32;  // 256 threads: 8 rows per pass
   for (int r = ty; r < 32; r += 8) t[r][tx] = H[(int64_t)(by + r) * Mp + bx + tx];
   __syncthreads();
-  for (int r = ty; r < 32; r += 8) J[(int64_t)(bx + r) * Mp + by + tx] = t[tx][r];
+  for (int r = ty; r < 32; r += 8) J[(int64_t)(bx + r) * mp + by + tx] = t[tx][r];
 }
 
 // ---- solve kernel -------------------------------------------------------------
 
-// One product of a sweep: out = c + s1 * (M1 v1) - (M2 v2) (absent terms null);
-// MT is the type of the stored blocks
+// One product of a sweep over the rows of a block: out = c + s1 * (M1 v1) - (M2
+// v2); a term holds for the rows r0 .. r0 + rows - 1 (row r0 is the matrix's row
+// 0; rows = 0: absent), over n columns with row stride ld (zeros from n to ld).
+// MT is the type of the stored blocks.
+template <typename MT>
+struct BtTerm {
+  const MT *M;
+  const double *v;
+  int r0, rows, n, ld;
+};
 template <typename MT>
 struct BtOp {
-  const MT *M1;
-  const double *v1;
-  const MT *M2;
-  const double *v2, *c;
+  BtTerm<MT> t1, t2;
+  const double *c;
   double *out;
   double s1;
+  int rows;  // of the block
 };
 
 __global__ void k_bt_narrow(int64_t n, const double *__restrict__ a, float *__restrict__ b) {
@@ -246,25 +294,26 @@ __global__ void k_bt_narrow(int64_t n, const double *__restrict__ a, float *__re
 // the same order for any NV (four strided partial sums per lane, then the wave
 // reduction).
 template <int NV, typename MT>
-__global__ __launch_bounds__(256) void k_bt_mv(int m, int Mp, BtOp<MT> o0, BtOp<MT> o1,
-                                               int64_t vs) {
+__global__ __launch_bounds__(256) void k_bt_mv(BtOp<MT> o0, BtOp<MT> o1, int rb, int64_t vs) {
   constexpr int W = 16 / (int)sizeof(MT);  // entries per 16-byte load
   struct alignas(16) Chunk {
     MT e[W];
   };
-  const int rb = (m + 3) / 4;
   const int which = (int)blockIdx.x >= rb;
   const BtOp<MT> &o = which ? o1 : o0;
   const int row = ((int)blockIdx.x - which * rb) * 4 + (int)(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
-  if (row >= m) return;  // whole wave
+  if (row >= o.rows) return;  // whole wave
   double a1[NV], a2[NV];
-  // The matrix row (16-byte aligned: Mp is a multiple of 32) streams as 16-byte
+  // The matrix row (16-byte aligned: ld is a multiple of 32) streams as 16-byte
   // loads of W entries, four per lane per step (256 W entries a wave), into four
   // partial sums per right side; x (L2 resident, any alignment) is read per
-  // entry.  (Issuing a whole row's loads before the first use, with the last
-  // chunk guarded entry by entry, measured slower.)
-  auto rowdot = [&](const MT *__restrict__ r, const double *__restrict__ x, double *acc) {
+  // entry.  The last step's loads are issued together too, each if it starts
+  // before ld; the row is zero from n on, where x is read at its last entry.
+  auto rowdot = [&](const BtTerm<MT> &t_, double *acc) {
+    const MT *__restrict__ r = t_.M + (int64_t)(row - t_.r0) * t_.ld;
+    const double *__restrict__ x = t_.v;
+    const int m = t_.n;
     double t[NV][4];
 #pragma unroll
     for (int v = 0; v < NV; ++v) t[v][0] = t[v][1] = t[v][2] = t[v][3] = 0.0;
@@ -285,32 +334,48 @@ __global__ __launch_bounds__(256) void k_bt_mv(int m, int Mp, BtOp<MT> o0, BtOp<
         }
       }
     }
-    for (int j = j0 + lane; j < m; j += 64) {
-      const double r0 = (double)r[j];
+    if (j0 < m) {
+      Chunk q[4];
 #pragma unroll
-      for (int v = 0; v < NV; ++v) t[v][0] += r0 * x[v * vs + j];
+      for (int u = 0; u < 4; ++u) {
+        const int j = j0 + 64 * W * u + W * lane;
+        if (j < t_.ld) {
+          q[u] = rc[j / W];
+        } else {
+#pragma unroll
+          for (int w = 0; w < W; ++w) q[u].e[w] = MT(0);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        if (j0 + 64 * W * u >= m) break;
+        const int j = j0 + 64 * W * u + W * lane;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+          const double *xv = x + v * vs;
+#pragma unroll
+          for (int w = 0; w < W; ++w)
+            t[v][u] += (double)q[u].e[w] * xv[j + w < m ? j + w : m - 1];
+        }
+      }
     }
 #pragma unroll
     for (int v = 0; v < NV; ++v) acc[v] = (t[v][0] + t[v][1]) + (t[v][2] + t[v][3]);
   };
-  if (o.M1) {
-    rowdot(o.M1 + (int64_t)row * Mp, o.v1, a1);
-  } else {
+  const bool in1 = row >= o.t1.r0 && row < o.t1.r0 + o.t1.rows;
+  const bool in2 = row >= o.t2.r0 && row < o.t2.r0 + o.t2.rows;
 #pragma unroll
-    for (int v = 0; v < NV; ++v) a1[v] = 0.0;
-  }
-  if (o.M2) {
-    rowdot(o.M2 + (int64_t)row * Mp, o.v2, a2);
-  } else {
+  for (int v = 0; v < NV; ++v) a1[v] = a2[v] = 0.0;
+  if (in1) rowdot(o.t1, a1);
+  if (in2) rowdot(o.t2, a2);
+  if (in1 || in2) {
 #pragma unroll
-    for (int v = 0; v < NV; ++v) a2[v] = 0.0;
-  }
+    for (int sh = 32; sh > 0; sh >>= 1) {
 #pragma unroll
-  for (int sh = 32; sh > 0; sh >>= 1) {
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      a1[v] += __shfl_xor(a1[v], sh, 64);
-      a2[v] += __shfl_xor(a2[v], sh, 64);
+      for (int v = 0; v < NV; ++v) {
+        a1[v] += __shfl_xor(a1[v], sh, 64);
+        a2[v] += __shfl_xor(a2[v], sh, 64);
+      }
     }
   }
   if (lane == 0) {
@@ -338,71 +403,66 @@ static void bt_invert(double *Gk, int Mp, int nbk, const double *diag, int *flag
   }
 }
 
+// the blocks of one factored operator
+template <typename MT>
+struct BtBlocks {
+  MT *g, *h, *j;
+  BtShape q;
+  MT *G(int k) const { return g + (int64_t)k * q.Mp * q.Mp; }
+  MT *H(int k) const { return h + (int64_t)k * q.mp * q.Mp; }
+  MT *J(int k) const { return j + (int64_t)k * q.mp * q.Mp; }
+  int plane0(int k) const { return k * q.g; }
+  int planes(int k) const { return std::min(q.g, q.K - k * q.g); }
+  int rows(int k) const { return planes(k) * q.m; }
+};
+
 void coarse_direct_setup(CoarseSolver &S, int64_t nx, int64_t ny, int64_t nz, hipStream_t s) {
-  const int m = (int)(nx * ny), K = (int)nz, c = K / 2;
-  const int Mp = (int)padded(m), nbk = Mp / kGB;
-  const int64_t M2 = (int64_t)Mp * Mp;
-  const unsigned g2 = nblk(M2);
+  const BtBlocks<double> D{S.dG, S.dH, S.dJ, S.shape};
+  const BtShape &q = S.shape;
+  const int B = q.B, c = B / 2, Mp = q.Mp, mp = q.mp, nbk = Mp / kGB;
+  const unsigned gT = nblk((int64_t)Mp * Mp), gH = nblk((int64_t)mp * Mp);
+  if (q.m != nx * ny || q.K != nz) fail(SEM_EINVAL, "coarse solve: blocks of another grid");
   SEM_HIP(hipMemsetAsync(S.dflag, 0, sizeof(int), s));
-  auto G = [&](int k) { return S.dG + k * M2; };
-  auto H = [&](int k) { return S.dH + k * M2; };
-  auto J = [&](int k) { return S.dJ + k * M2; };
-  // chain from plane 0 up to c - 1
-  for (int k = 0; k < c; ++k) {
-    if (k > 0) {
-      hipLaunchKernelGGL(k_bt_H, dim3(g2), dim3(256), 0, s, (int)nx, (int)ny, S.n, k, Mp, S.St,
-                         (const double *)G(k - 1), H(k), -1);
-      SEM_LAUNCH("k_bt_H");
-    }
-    hipLaunchKernelGGL(k_bt_T, dim3(g2), dim3(256), 0, s, (int)nx, (int)ny, S.n, k, Mp, S.St,
-                       k > 0 ? (const double *)H(k) : nullptr, -1, (const double *)nullptr, 0,
-                       G(k), S.dy);
-    SEM_LAUNCH("k_bt_T");
-    bt_invert(G(k), Mp, nbk, S.dy, S.dflag, s);
-  }
-  // chain from plane K - 1 down to c + 1
-  for (int k = K - 1; k > c; --k) {
-    if (k < K - 1) {
-      hipLaunchKernelGGL(k_bt_H, dim3(g2), dim3(256), 0, s, (int)nx, (int)ny, S.n, k, Mp, S.St,
-                         (const double *)G(k + 1), H(k), 1);
-      SEM_LAUNCH("k_bt_H");
-    }
-    hipLaunchKernelGGL(k_bt_T, dim3(g2), dim3(256), 0, s, (int)nx, (int)ny, S.n, k, Mp, S.St,
-                       k < K - 1 ? (const double *)H(k) : nullptr, 1, (const double *)nullptr, 0,
-                       G(k), S.dy);
-    SEM_LAUNCH("k_bt_T");
-    bt_invert(G(k), Mp, nbk, S.dy, S.dflag, s);
-  }
-  // plane c takes both updates: from below in H's slot, from above in J's slot
-  if (c > 0) {
-    hipLaunchKernelGGL(k_bt_H, dim3(g2), dim3(256), 0, s, (int)nx, (int)ny, S.n, c, Mp, S.St,
-                       (const double *)G(c - 1), H(c), -1);
+  // H of block k towards k + dz, into `out`
+  auto make_h = [&](int k, int dz, double *out) {
+    const int nb = k + dz, plane = dz < 0 ? D.plane0(k) : D.plane0(k) + D.planes(k) - 1;
+    hipLaunchKernelGGL(k_bt_H, dim3(gH), dim3(256), 0, s, (int)nx, (int)ny, S.n, plane, D.rows(nb),
+                       mp, Mp, dz < 0 ? D.rows(nb) - q.m : 0, S.St, (const double *)D.G(nb), out, dz);
     SEM_LAUNCH("k_bt_H");
+  };
+  // T_k from the updates from below (hd) and above (hu), inverted in place
+  auto make_g = [&](int k, const double *hd, const double *hu) {
+    hipLaunchKernelGGL(k_bt_T, dim3(gT), dim3(256), 0, s, (int)nx, (int)ny, S.n, D.plane0(k),
+                       D.planes(k), Mp, S.St, hd, hd ? D.rows(k - 1) - q.m : 0, hu, D.G(k), S.dy);
+    SEM_LAUNCH("k_bt_T");
+    bt_invert(D.G(k), Mp, nbk, S.dy, S.dflag, s);
+  };
+  for (int k = 0; k < c; ++k) {  // chain from block 0 up to c - 1
+    if (k > 0) make_h(k, -1, D.H(k));
+    make_g(k, k > 0 ? D.H(k) : nullptr, nullptr);
   }
-  if (c < K - 1) {
-    hipLaunchKernelGGL(k_bt_H, dim3(g2), dim3(256), 0, s, (int)nx, (int)ny, S.n, c, Mp, S.St,
-                       (const double *)G(c + 1), J(c), 1);
-    SEM_LAUNCH("k_bt_H");
+  for (int k = B - 1; k > c; --k) {  // chain from block B - 1 down to c + 1
+    if (k < B - 1) make_h(k, 1, D.H(k));
+    make_g(k, nullptr, k < B - 1 ? D.H(k) : nullptr);
   }
-  hipLaunchKernelGGL(k_bt_T, dim3(g2), dim3(256), 0, s, (int)nx, (int)ny, S.n, c, Mp, S.St,
-                     c > 0 ? (const double *)H(c) : nullptr, -1,
-                     c < K - 1 ? (const double *)J(c) : nullptr, 1, G(c), S.dy);
-  SEM_LAUNCH("k_bt_T");
-  bt_invert(G(c), Mp, nbk, S.dy, S.dflag, s);
+  // block c takes both updates: from below in H's slot, from above in J's slot
+  if (c > 0) make_h(c, -1, D.H(c));
+  if (c < B - 1) make_h(c, 1, D.J(c));
+  make_g(c, c > 0 ? D.H(c) : nullptr, c < B - 1 ? D.J(c) : nullptr);
   // back-substitution blocks: J_k = H_{k+1}^T below c, H_{k-1}^T above c (Hu_c for c + 1)
-  for (int k = 0; k < K; ++k) {
+  for (int k = 0; k < B; ++k) {
     if (k == c) continue;
-    const double *src = k < c ? H(k + 1) : (k - 1 == c ? J(c) : H(k - 1));
-    hipLaunchKernelGGL(k_bt_transpose, dim3(nbk, nbk), dim3(256), 0, s, Mp, src, J(k));
+    const double *src = k < c ? D.H(k + 1) : (k - 1 == c ? D.J(c) : D.H(k - 1));
+    hipLaunchKernelGGL(k_bt_transpose, dim3(Mp / 32, mp / 32), dim3(256), 0, s, mp, Mp, src, D.J(k));
     SEM_LAUNCH("k_bt_transpose");
   }
   if (S.fG) {
-    const int64_t nb = (int64_t)K * M2;
-    hipLaunchKernelGGL(k_bt_narrow, dim3(nblk(nb)), dim3(256), 0, s, nb, (const double *)S.dG,
+    const int64_t ng = (int64_t)B * Mp * Mp, nh = (int64_t)B * mp * Mp;
+    hipLaunchKernelGGL(k_bt_narrow, dim3(nblk(ng)), dim3(256), 0, s, ng, (const double *)S.dG,
                        S.fG);
-    hipLaunchKernelGGL(k_bt_narrow, dim3(nblk(nb)), dim3(256), 0, s, nb, (const double *)S.dH,
+    hipLaunchKernelGGL(k_bt_narrow, dim3(nblk(nh)), dim3(256), 0, s, nh, (const double *)S.dH,
                        S.fH);
-    hipLaunchKernelGGL(k_bt_narrow, dim3(nblk(nb)), dim3(256), 0, s, nb, (const double *)S.dJ,
+    hipLaunchKernelGGL(k_bt_narrow, dim3(nblk(nh)), dim3(256), 0, s, nh, (const double *)S.dJ,
                        S.fJ);
     SEM_LAUNCH("k_bt_narrow");
   }
@@ -413,77 +473,86 @@ void coarse_direct_setup(CoarseSolver &S, int64_t nx, int64_t ny, int64_t nz, hi
 }
 
 template <int NV, typename MT>
-static void bt_sweeps(const CoarseSolver &S, const MT *dG, const MT *dH, const MT *dJ, int m,
-                      int K, int Mp, const double *b, double *x, double *y, hipStream_t s) {
+static void bt_sweeps(const BtBlocks<MT> &D, int64_t vs, const double *b, double *x, double *y,
+                      hipStream_t s) {
   using BtOp = sem::BtOp<MT>;
-  const int64_t M2 = (int64_t)Mp * Mp, vs = S.n;
-  const int c = K / 2;
-  const unsigned rb = (unsigned)((m + 3) / 4);
-  auto G = [&](int k) { return dG + k * M2; };
-  auto H = [&](int k) { return dH + k * M2; };
-  auto J = [&](int k) { return dJ + k * M2; };
-  // y_k of the sweep; y_0 and y_{K-1} are b itself
-  auto Y = [&](int k) -> const double * {
-    return (k == 0 || k == K - 1) ? b + (int64_t)k * m : (const double *)(y + (int64_t)k * m);
-  };
+  using BtTerm = sem::BtTerm<MT>;
+  const BtShape &q = D.q;
+  const int B = q.B, c = B / 2, m = q.m;
+  const BtTerm none{nullptr, nullptr, 0, 0, 0, 1};
+  auto at = [&](const double *v, int k) { return v + (int64_t)D.plane0(k) * m; };
+  auto to = [&](double *v, int k) { return v + (int64_t)D.plane0(k) * m; };
+  // y_k of the sweep; y_0 and y_{B-1} are b itself (unless they are block c)
+  auto Y = [&](int k) { return (k == 0 || k == B - 1) && k != c ? at(b, k) : at(y, k); };
   auto launch = [&](const BtOp &o0, const BtOp *o1) {
-    const BtOp none{};
-    hipLaunchKernelGGL((k_bt_mv<NV, MT>), dim3(o1 ? 2 * rb : rb), dim3(256), 0, s, m, Mp, o0,
-                       o1 ? *o1 : none, vs);
+    const BtOp empty{};
+    const int rows = std::max(o0.rows, o1 ? o1->rows : 0), rb = (rows + 3) / 4;
+    hipLaunchKernelGGL((k_bt_mv<NV, MT>), dim3(o1 ? 2 * rb : rb), dim3(256), 0, s, o0,
+                       o1 ? *o1 : empty, rb, vs);
     SEM_LAUNCH("k_bt_mv");
   };
+  // the terms H_k v (v of the block below, dz = -1, or above), G_k v, J_k v (v
+  // of the plane of the neighbouring block next to k)
+  auto h_term = [&](const MT *H, int k, int dz) {
+    return BtTerm{H, Y(k + dz), dz < 0 ? 0 : D.rows(k) - m, m, D.rows(k + dz), q.Mp};
+  };
+  auto g_term = [&](int k, const double *v) { return BtTerm{D.G(k), v, 0, D.rows(k), D.rows(k), q.Mp}; };
+  auto j_term = [&](int k, int dz) {
+    const double *v = dz > 0 ? at(x, k + 1) : at(x, k - 1) + (D.rows(k - 1) - m);
+    return BtTerm{D.J(k), v, 0, D.rows(k), m, q.mp};
+  };
+  if (B == 1) {  // one block: x = G b
+    launch(BtOp{g_term(0, b), none, nullptr, x, 1.0, D.rows(0)}, nullptr);
+    return;
+  }
   // inwards: y_k = b_k - H_k y_{k-1} (k < c), y_k = b_k - H_k y_{k+1} (k > c)
   for (int t = 1;; ++t) {
-    const int kd = t, ku = K - 1 - t;
+    const int kd = t, ku = B - 1 - t;
     const bool dn = kd < c, up = ku > c;
     if (!dn && !up) break;
-    BtOp od{H(kd), Y(kd - 1), nullptr, nullptr, b + (int64_t)kd * m, y + (int64_t)kd * m, -1.0};
-    BtOp ou{H(ku), Y(ku + 1), nullptr, nullptr, b + (int64_t)ku * m, y + (int64_t)ku * m, -1.0};
+    BtOp od{}, ou{};
+    if (dn) od = BtOp{h_term(D.H(kd), kd, -1), none, at(b, kd), to(y, kd), -1.0, D.rows(kd)};
+    if (up) ou = BtOp{h_term(D.H(ku), ku, 1), none, at(b, ku), to(y, ku), -1.0, D.rows(ku)};
     if (dn && up) launch(od, &ou);
     else launch(dn ? od : ou, nullptr);
   }
-  // plane c: y_c = b_c - Hd_c y_{c-1} - Hu_c y_{c+1}; x_c = G_c y_c
-  {
-    BtOp oy{c > 0 ? H(c) : nullptr, c > 0 ? Y(c - 1) : nullptr, c < K - 1 ? J(c) : nullptr,
-            c < K - 1 ? Y(c + 1) : nullptr, b + (int64_t)c * m, y + (int64_t)c * m, -1.0};
-    launch(oy, nullptr);
-    BtOp ox{G(c), y + (int64_t)c * m, nullptr, nullptr, nullptr, x + (int64_t)c * m, 1.0};
-    launch(ox, nullptr);
-  }
+  // block c: y_c = b_c - Hd_c y_{c-1} - Hu_c y_{c+1}; x_c = G_c y_c
+  launch(BtOp{c > 0 ? h_term(D.H(c), c, -1) : none, c < B - 1 ? h_term(D.J(c), c, 1) : none, at(b, c),
+              to(y, c), -1.0, D.rows(c)},
+         nullptr);
+  launch(BtOp{g_term(c, at(y, c)), none, nullptr, to(x, c), 1.0, D.rows(c)}, nullptr);
   // outwards: x_k = G_k y_k - J_k x_{k+1} (k < c), x_k = G_k y_k - J_k x_{k-1} (k > c)
   for (int t = 1;; ++t) {
     const int kd = c - t, ku = c + t;
-    const bool dn = kd >= 0, up = ku < K;
+    const bool dn = kd >= 0, up = ku < B;
     if (!dn && !up) break;
-    BtOp od{G(kd), Y(kd), J(kd), x + (int64_t)(kd + 1) * m, nullptr, x + (int64_t)kd * m, 1.0};
-    BtOp ou{G(ku), Y(ku), J(ku), x + (int64_t)(ku - 1) * m, nullptr, x + (int64_t)ku * m, 1.0};
+    BtOp od{}, ou{};
+    if (dn) od = BtOp{g_term(kd, Y(kd)), j_term(kd, 1), nullptr, to(x, kd), 1.0, D.rows(kd)};
+    if (up) ou = BtOp{g_term(ku, Y(ku)), j_term(ku, -1), nullptr, to(x, ku), 1.0, D.rows(ku)};
     if (dn && up) launch(od, &ou);
     else launch(dn ? od : ou, nullptr);
   }
 }
 
 template <typename MT>
-static void bt_apply(const CoarseSolver &S, const MT *G, const MT *H, const MT *J, int m, int K,
-                     int Mp, const double *b, double *x, hipStream_t s, int nv) {
+static void bt_apply(const CoarseSolver &S, const BtBlocks<MT> &D, const double *b, double *x,
+                     hipStream_t s, int nv) {
   for (int v0 = 0; v0 < nv; v0 += 4) {  // up to four right sides per sweep
     const int64_t o = (int64_t)v0 * S.n;
     switch (std::min(4, nv - v0)) {
-      case 1: bt_sweeps<1, MT>(S, G, H, J, m, K, Mp, b + o, x + o, S.dy + o, s); break;
-      case 2: bt_sweeps<2, MT>(S, G, H, J, m, K, Mp, b + o, x + o, S.dy + o, s); break;
-      case 3: bt_sweeps<3, MT>(S, G, H, J, m, K, Mp, b + o, x + o, S.dy + o, s); break;
-      default: bt_sweeps<4, MT>(S, G, H, J, m, K, Mp, b + o, x + o, S.dy + o, s); break;
+      case 1: bt_sweeps<1, MT>(D, S.n, b + o, x + o, S.dy + o, s); break;
+      case 2: bt_sweeps<2, MT>(D, S.n, b + o, x + o, S.dy + o, s); break;
+      case 3: bt_sweeps<3, MT>(D, S.n, b + o, x + o, S.dy + o, s); break;
+      default: bt_sweeps<4, MT>(D, S.n, b + o, x + o, S.dy + o, s); break;
     }
   }
 }
 
-void coarse_direct_apply(const CoarseSolver &S, int64_t nx, int64_t ny, int64_t nz, const double *b,
-                         double *x, hipStream_t s, int nv) {
-  const int m = (int)(nx * ny), K = (int)nz;
-  const int Mp = (int)padded(m);
+void coarse_direct_apply(const CoarseSolver &S, const double *b, double *x, hipStream_t s, int nv) {
   if (S.fG)
-    bt_apply<float>(S, S.fG, S.fH, S.fJ, m, K, Mp, b, x, s, nv);
+    bt_apply<float>(S, BtBlocks<float>{S.fG, S.fH, S.fJ, S.shape}, b, x, s, nv);
   else
-    bt_apply<double>(S, S.dG, S.dH, S.dJ, m, K, Mp, b, x, s, nv);
+    bt_apply<double>(S, BtBlocks<double>{S.dG, S.dH, S.dJ, S.shape}, b, x, s, nv);
 }
 
 }  // namespace sem

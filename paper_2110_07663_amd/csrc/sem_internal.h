@@ -173,6 +173,12 @@ struct CoarseScalars {
   int aborted;  // set when a grid barrier of the persistent solve timed out
 };
 
+// blocks of the exact coarse solve: K planes of m nodes, g planes per block, B
+// blocks; a block's and a plane's nodes rounded up to 32
+struct BtShape {
+  int m, K, g, B, Mp, mp;
+};
+
 // assembled p = 1 coarse operator and its CG state (buffers in the workspace)
 struct CoarseSolver {
   int64_t n = 0;                   // global nodes of the coarsest level
@@ -190,6 +196,7 @@ struct CoarseSolver {
   bool persistent = false;         // whole solve in one cooperative launch
   // exact block-tridiagonal solve (coarse_direct.hip): G, H, J blocks, work vector
   bool direct = false;
+  BtShape shape{};
   double *dG = nullptr, *dH = nullptr, *dJ = nullptr, *dy = nullptr;
   float *fG = nullptr, *fH = nullptr, *fJ = nullptr;  // FP32 copies read by the sweeps (FP32 smoother)
   int *dflag = nullptr;
@@ -450,11 +457,11 @@ struct CoarseRhs {
 void coarse_solve_assembled(Ctx &c, Level &C, double tol, int maxit, hipStream_t s, int nv = 1,
                             CoarseRhs u = {});
 void coarse_release(CoarseSolver &S);
-size_t coarse_direct_bytes(int64_t nx, int64_t ny, int64_t nz, bool f32);
+BtShape coarse_direct_shape(int64_t nx, int64_t ny, int64_t nz, bool f32);
 void coarse_direct_setup(CoarseSolver &S, int64_t nx, int64_t ny, int64_t nz, hipStream_t s);
 // nv right sides, S.n apart in b, x and the work vector S.dy
-void coarse_direct_apply(const CoarseSolver &S, int64_t nx, int64_t ny, int64_t nz, const double *b,
-                         double *x, hipStream_t s, int nv = 1);
+void coarse_direct_apply(const CoarseSolver &S, const double *b, double *x, hipStream_t s,
+                         int nv = 1);
 
 // hessenberg.cpp
 double hessenberg_max_abs_eig(const double *H, int ldh, int k);

@@ -249,21 +249,24 @@ static void layout(Ctx &c, const sem_mesh *m, Arena &A, SetupScratch &sc) {
       // FP32 smoother: the sweeps read FP32 copies of the blocks (SEM_COARSE_F64=1 keeps FP64)
       const char *cf = getenv("SEM_COARSE_F64");
       const bool f32 = lowp && !(cf && cf[0] == '1');
-      const size_t db = coarse_direct_bytes(nx, ny, nz, false);
+      // by default where the blocks of single planes would take up to 4 GiB
+      const int64_t plane = (nx * ny + 31) / 32 * 32;
+      const size_t db = (size_t)(3 * nz * plane * plane + nx * ny * nz) * sizeof(double);
       const bool want = o.coarse_solver == 1 || (o.coarse_solver < 0 && db <= ((size_t)4 << 30));
       S.direct = false;
       S.dG = S.dH = S.dJ = S.dy = nullptr;
       S.fG = S.fH = S.fJ = nullptr;
       S.dflag = nullptr;
       if (want) {
-        const int64_t Mp = (nx * ny + 31) / 32 * 32;
-        S.dG = A.take<double>((size_t)(nz * Mp * Mp));
-        S.dH = A.take<double>((size_t)(nz * Mp * Mp));
-        S.dJ = A.take<double>((size_t)(nz * Mp * Mp));
+        S.shape = coarse_direct_shape(nx, ny, nz, f32);
+        const int64_t Mp = S.shape.Mp, ng = S.shape.B * Mp * Mp, nh = S.shape.B * Mp * S.shape.mp;
+        S.dG = A.take<double>((size_t)ng);
+        S.dH = A.take<double>((size_t)nh);
+        S.dJ = A.take<double>((size_t)nh);
         if (f32) {
-          S.fG = A.take<float>((size_t)(nz * Mp * Mp));
-          S.fH = A.take<float>((size_t)(nz * Mp * Mp));
-          S.fJ = A.take<float>((size_t)(nz * Mp * Mp));
+          S.fG = A.take<float>((size_t)ng);
+          S.fH = A.take<float>((size_t)nh);
+          S.fJ = A.take<float>((size_t)nh);
         }
         S.dy = A.take<double>(std::max<size_t>(nv * S.n, Mp));  // also the pivot-test diagonal
         S.dflag = A.take<int>(64);
