@@ -67,15 +67,17 @@ template <typename T>
 __global__ void k_scale(int64_t n, const T *__restrict__ w, const T *__restrict__ x,
                         T *__restrict__ y) {
   int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (t < n) y[t] = w[t] * x[t];
+  const int64_t o = blockIdx.y * n + t;  // right side blockIdx.y
+  if (t < n) y[o] = w[t] * x[o];
 }
 template <typename T>
-void launch_scale(int64_t n, const T *w, const T *x, T *y, hipStream_t s) {
-  hipLaunchKernelGGL(k_scale<T>, dim3(nb(n, 256)), dim3(256), 0, s, n, w, x, y);
+void launch_scale(int64_t n, const T *w, const T *x, T *y, hipStream_t s, int nv) {
+  hipLaunchKernelGGL(k_scale<T>, dim3(nb(n, 256), (unsigned)nv), dim3(256), 0, s, n, w, x, y);
   SEM_LAUNCH("k_scale");
 }
-template void launch_scale<double>(int64_t, const double *, const double *, double *, hipStream_t);
-template void launch_scale<float>(int64_t, const float *, const float *, float *, hipStream_t);
+template void launch_scale<double>(int64_t, const double *, const double *, double *, hipStream_t,
+                                   int);
+template void launch_scale<float>(int64_t, const float *, const float *, float *, hipStream_t, int);
 
 __global__ void k_d2f(int64_t n, const double *__restrict__ x, float *__restrict__ y) {
   int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
@@ -123,86 +125,134 @@ void launch_sub(int64_t n, const T *a, const T *b, T *y, hipStream_t s) {
 template void launch_sub<double>(int64_t, const double *, const double *, double *, hipStream_t);
 template void launch_sub<float>(int64_t, const float *, const float *, float *, hipStream_t);
 
-// one pass of the loop body: x += d_k; r -= S A d_k (= t); d = a d_k + c r
-// (xz: x is zero on entry and is not read)
-// t read as assembled (XD::value false), or with the deferred x step of the
-// gather-scatter taken on the way (16-byte vectors VT of T; a vector never
-// straddles an element row, so only its first lane can be an i = 0 node and
-// only its last an i = p node).  The kernels that read this way take their
-// blocks in XCD-contiguous order (xcd_block), so the x-neighbour copies they
-// read mostly come from rows the same XCD reads: its own L2.
+// How a Chebyshev update reads t = S A d:
+//  kAsIs  t is assembled.
+//  kXY    with the deferred x (and y) step of the gather-scatter taken on the way
+//         (16-byte vectors VT of T; a vector never straddles an element row, so
+//         only its first lane can be an i = 0 node and only its last an i = p
+//         node).  The kernels that read this way take their blocks in
+//         XCD-contiguous order (xcd_block), so the x-neighbour copies they read
+//         mostly come from rows the same XCD reads: its own L2.
+//  kAll   no step was taken: every node sums its up to 8 copies, the x, then the
+//         y, then the z pairs, each as (upper end of the lower element + lower end
+//         of the upper), as the passes do (entry by entry, any N).
+// DI: t = dinv times what is read (Jacobi: S is diagonal, and acts on A d).
+enum : int { kAsIs = 0, kXY = 1, kAll = 2 };
 struct XDev {
   unsigned nex, ney, N, p, vrow, vel, vside;  // vectors per row, per element, per right side
   int bc0, bc1, bc2, bc3;
   int y;  // the y step is deferred too (taken before the x step)
+  unsigned nez;
+  int bc4, bc5;
+  const void *di;  // DI: 1 / diag(A), one right side
 };
-template <typename XD, typename VT>
-__device__ inline VT read_t(const VT *__restrict__ tv, int64_t m, const XDev &f) {
+// entry m of several right sides within its own (one right side: no division)
+__device__ inline unsigned within(int64_t m, unsigned side) {
+  return m < (int64_t)side ? (unsigned)m : (unsigned)(m % side);
+}
+template <typename VT>
+__device__ inline VT read_xy(const VT *__restrict__ tv, int64_t m, const XDev &f) {
   VT v = tv[m];
-  if constexpr (XD::value) {
-    using T = std::decay_t<decltype(v[0])>;
-    constexpr int W = sizeof(VT) / sizeof(T);
-    const T *__restrict__ ts = reinterpret_cast<const T *>(tv);
-    const unsigned mq = (unsigned)(m % f.vside);
-    const unsigned e = mq / f.vel;
-    const unsigned vi = mq - e * f.vel;
-    const unsigned i0 = vi % f.vrow * W;
-    const unsigned ex = e % f.nex;
-    const int64_t q = m * W;
-    const int64_t N3 = (int64_t)f.vel * W;
-    // y step (rows j = 0 and j = p): (p-row of the lower element + 0-row of the
-    // upper), Dirichlet y-faces zero; ys gives the same for one x-neighbour value
-    int ymode = 0;  // 0 none, 1 j = 0 with a lower copy, 2 j = p with an upper copy, 3 zero
-    int64_t yoff = 0;
-    if (f.y) {
-      const unsigned j = (vi / f.vrow) % f.N;
-      const unsigned ey = (e / f.nex) % f.ney;
-      yoff = (int64_t)f.nex * N3 - (int64_t)f.p * f.N;
-      if (j == 0)
-        ymode = ey > 0 ? 1 : (f.bc2 ? 3 : 0);
-      else if (j == f.p)
-        ymode = ey + 1 < f.ney ? 2 : (f.bc3 ? 3 : 0);
-      if (ymode == 1)
-        v = tv[m - yoff / W] + v;
-      else if (ymode == 2)
-        v = v + tv[m + yoff / W];
-      else if (ymode == 3)
-        v = VT(T(0));
-    }
-    auto ys = [&](int64_t idx) -> T {
-      const T own = ts[idx];
-      if (ymode == 1) return ts[idx - yoff] + own;
-      if (ymode == 2) return own + ts[idx + yoff];
-      if (ymode == 3) return T(0);
-      return own;
-    };
-    if (i0 == 0) {
-      if (ex > 0)
-        v[0] = ys(q - N3 + f.p) + v[0];
-      else if (f.bc0)
-        v[0] = T(0);
-    }
-    if (i0 + W - 1 == f.p) {
-      if (ex + 1 < f.nex)
-        v[W - 1] = v[W - 1] + ys(q + (W - 1) - f.p + N3);
-      else if (f.bc1)
-        v[W - 1] = T(0);
-    }
+  using T = std::decay_t<decltype(v[0])>;
+  constexpr int W = sizeof(VT) / sizeof(T);
+  const T *__restrict__ ts = reinterpret_cast<const T *>(tv);
+  const unsigned mq = within(m, f.vside);
+  const unsigned e = mq / f.vel;
+  const unsigned vi = mq - e * f.vel;
+  const unsigned i0 = vi % f.vrow * W;
+  const unsigned ex = e % f.nex;
+  const int64_t q = m * W;
+  const int64_t N3 = (int64_t)f.vel * W;
+  // y step (rows j = 0 and j = p): (p-row of the lower element + 0-row of the
+  // upper), Dirichlet y-faces zero; ys gives the same for one x-neighbour value
+  int ymode = 0;  // 0 none, 1 j = 0 with a lower copy, 2 j = p with an upper copy, 3 zero
+  int64_t yoff = 0;
+  if (f.y) {
+    const unsigned j = (vi / f.vrow) % f.N;
+    const unsigned ey = (e / f.nex) % f.ney;
+    yoff = (int64_t)f.nex * N3 - (int64_t)f.p * f.N;
+    if (j == 0)
+      ymode = ey > 0 ? 1 : (f.bc2 ? 3 : 0);
+    else if (j == f.p)
+      ymode = ey + 1 < f.ney ? 2 : (f.bc3 ? 3 : 0);
+    if (ymode == 1)
+      v = tv[m - yoff / W] + v;
+    else if (ymode == 2)
+      v = v + tv[m + yoff / W];
+    else if (ymode == 3)
+      v = VT(T(0));
+  }
+  auto ys = [&](int64_t idx) -> T {
+    const T own = ts[idx];
+    if (ymode == 1) return ts[idx - yoff] + own;
+    if (ymode == 2) return own + ts[idx + yoff];
+    if (ymode == 3) return T(0);
+    return own;
+  };
+  if (i0 == 0) {
+    if (ex > 0)
+      v[0] = ys(q - N3 + f.p) + v[0];
+    else if (f.bc0)
+      v[0] = T(0);
+  }
+  if (i0 + W - 1 == f.p) {
+    if (ex + 1 < f.nex)
+      v[W - 1] = v[W - 1] + ys(q + (W - 1) - f.p + N3);
+    else if (f.bc1)
+      v[W - 1] = T(0);
   }
   return v;
 }
-
-template <typename T, typename XD = std::false_type>
-__global__ void k_cheb_update(int64_t n, T *__restrict__ x, T *__restrict__ r, T *__restrict__ d,
-                              const T *__restrict__ tv, T a, T c, int xz, XDev f) {
-  int64_t t = xcd_block() * (int64_t)blockDim.x + threadIdx.x;
-  if (t >= n) return;
-  T dk = d[t];
-  x[t] = xz ? dk : x[t] + dk;
-  T rn = r[t] - read_t<XD>(tv, t, f);
-  r[t] = rn;
-  d[t] = a * dk + c * rn;
+// (vrow, vel and vside count entries here)
+template <typename T>
+__device__ inline T read_all(const T *__restrict__ tv, int64_t m, const XDev &f) {
+  const unsigned mq = within(m, f.vside);
+  const unsigned e = mq / f.vel, q = mq - e * f.vel;
+  const unsigned jk = q / f.N, i = q - jk * f.N, k = jk / f.N, j = jk - k * f.N;
+  const unsigned ee = e / f.nex, ex = e - ee * f.nex, ez = ee / f.ney, ey = ee - ez * f.ney;
+  bool zero = false;
+  // per direction: offsets of the lower and the upper copy, and whether there are two
+  int o[3][2];
+  bool two[3];
+  auto side = [&](int d, unsigned c, unsigned at, unsigned n, int step, int b0, int b1) {
+    const bool lw = c == 0 && at > 0, up = c == f.p && at + 1 < n;
+    o[d][0] = lw ? -step : 0;
+    o[d][1] = up ? step : 0;
+    two[d] = lw || up;
+    zero = zero || (c == 0 && at == 0 && b0) || (c == f.p && at + 1 == n && b1);
+  };
+  const int N3 = (int)f.vel, N = (int)f.N, p = (int)f.p;
+  side(0, i, ex, f.nex, N3 - p, f.bc0, f.bc1);
+  side(1, j, ey, f.ney, (int)f.nex * N3 - p * N, f.bc2, f.bc3);
+  side(2, k, ez, f.nez, (int)(f.nex * f.ney) * N3 - p * N * N, f.bc4, f.bc5);
+  const T *__restrict__ at = tv + m;
+  T s[2][2][2];  // all eight loads issue; an absent copy reads the node itself
+#pragma unroll
+  for (int z = 0; z < 2; ++z)
+#pragma unroll
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+      for (int x = 0; x < 2; ++x) s[z][y][x] = at[o[0][x] + o[1][y] + o[2][z]];
+  T yz[2][2], zs[2];
+#pragma unroll
+  for (int z = 0; z < 2; ++z) {
+#pragma unroll
+    for (int y = 0; y < 2; ++y) yz[z][y] = two[0] ? s[z][y][0] + s[z][y][1] : s[z][y][0];
+    zs[z] = two[1] ? yz[z][0] + yz[z][1] : yz[z][0];
+  }
+  const T v = two[2] ? zs[0] + zs[1] : zs[0];
+  return zero ? T(0) : v;
 }
+template <int XD, bool DI, typename VT>
+__device__ inline VT read_t(const VT *__restrict__ tv, int64_t m, const XDev &f) {
+  VT v;
+  if constexpr (XD == kXY) v = read_xy(tv, m, f);
+  else if constexpr (XD == kAll) v = read_all(tv, m, f);
+  else v = tv[m];
+  if constexpr (DI) v *= reinterpret_cast<const VT *>(f.di)[within(m, f.vside)];
+  return v;
+}
+
 template <typename T>
 bool cheb_can_defer_x(int N, int64_t n, std::initializer_list<const void *> ps) {
   return N % (int)(16 / sizeof(T)) == 0 && vec16_ok<T>(n, ps);
@@ -210,10 +260,12 @@ bool cheb_can_defer_x(int N, int64_t n, std::initializer_list<const void *> ps) 
 template bool cheb_can_defer_x<float>(int, int64_t, std::initializer_list<const void *>);
 template bool cheb_can_defer_x<double>(int, int64_t, std::initializer_list<const void *>);
 
+// W: entries per vector of the kernel
 template <typename T>
-static XDev xdev(const XDefer &xd) {
-  constexpr unsigned W = 16 / sizeof(T);
+static XDev xdev(const XDefer &xd, unsigned W = 16 / sizeof(T)) {
   XDev f{};
+  f.vside = xd.nloc ? (unsigned)(xd.nloc / W) : 1u;
+  f.di = xd.dinv;
   if (!xd.on) return f;
   if (xd.N % (int)W != 0 || xd.nloc % ((int64_t)xd.N * xd.N * xd.N) != 0)
     fail(SEM_EINVAL, "deferred x step: vectors straddle element rows");
@@ -222,46 +274,45 @@ static XDev xdev(const XDefer &xd) {
   f.p = (unsigned)xd.N - 1;
   f.vrow = (unsigned)xd.N / W;
   f.vel = (unsigned)(xd.N * xd.N * xd.N) / W;
-  f.vside = (unsigned)(xd.nloc / W);
   f.bc0 = xd.bc0;
   f.bc1 = xd.bc1;
   f.y = xd.y ? 1 : 0;
   f.ney = (unsigned)xd.ney;
   f.bc2 = xd.bc2;
   f.bc3 = xd.bc3;
+  f.nez = (unsigned)xd.nez;
+  f.bc4 = xd.bc4;
+  f.bc5 = xd.bc5;
   return f;
 }
 
+// Streams are marked non-temporal (in the form that reads neighbours' copies,
+// which should stay in L2) only where the update's five vectors exceed the 256 MB
+// last-level cache; smaller ones are found there by the next kernel.
 template <typename T>
-void launch_cheb_update(int64_t n, T *x, T *r, T *d, const T *t, T a, T c, hipStream_t s,
-                        bool x_zero, const XDefer &xd) {
-  const XDev f = xdev<T>(xd);
-  if (vec16_ok<T>(n, {x, r, d, t})) {
-    using VT = typename V16<T>::type;
-    const int64_t m = n / (int64_t)(16 / sizeof(T));
-    if (xd.on)
-      hipLaunchKernelGGL((k_cheb_update<VT, std::true_type>), dim3(nb(m, 256)), dim3(256), 0, s, m,
-                         (VT *)x, (VT *)r, (VT *)d, (const VT *)t, (VT)a, (VT)c, (int)x_zero, f);
-    else
-      hipLaunchKernelGGL((k_cheb_update<VT>), dim3(nb(m, 256)), dim3(256), 0, s, m, (VT *)x,
-                         (VT *)r, (VT *)d, (const VT *)t, (VT)a, (VT)c, (int)x_zero, f);
-  } else {
-    if (xd.on) fail(SEM_EINVAL, "deferred x step needs the vector form");
-    hipLaunchKernelGGL((k_cheb_update<T>), dim3(nb(n, 256)), dim3(256), 0, s, n, x, r, d, t, a, c,
-                       (int)x_zero, f);
-  }
-  SEM_LAUNCH("k_cheb_update");
+static bool cheb_streams(int64_t n) {
+  return n * (int64_t)sizeof(T) > (int64_t)48 << 20;
 }
-template void launch_cheb_update<double>(int64_t, double *, double *, double *, const double *,
-                                         double, double, hipStream_t, bool, const XDefer &);
-template void launch_cheb_update<float>(int64_t, float *, float *, float *, const float *, float,
-                                        float, hipStream_t, bool, const XDefer &);
+
+// one pass of the loop body: x += d_k; r -= S A d_k (= t); d = a d_k + c r
+// (xz: x is zero on entry and is not read)
+template <typename T, int XD, bool DI, bool NTL>
+__global__ void k_cheb_update(int64_t n, T *__restrict__ x, T *__restrict__ r, T *__restrict__ d,
+                              const T *__restrict__ tv, T a, T c, int xz, XDev f) {
+  int64_t t = xcd_block() * (int64_t)blockDim.x + threadIdx.x;
+  if (t >= n) return;
+  T dk = d[t];
+  x[t] = xz ? dk : x[t] + dk;
+  T rn = r[t] - read_t<XD, DI>(tv, t, f);
+  r[t] = rn;
+  d[t] = a * dk + c * rn;
+}
 
 // The first pass of the loop without forming d_0 = r_0 / theta beforehand: A
 // and S are linear, so the caller applies them to r_0 and this pass scales
 // (tv = S A r_0).  x += d_0; r -= tv / theta; d = a d_0 + c r; with `last` the
 // closing x += d as well (r and d then unwritten).  xz: x is zero on entry.
-template <typename T, typename XD = std::false_type, bool NTL = false>
+template <typename T, int XD, bool DI, bool NTL>
 __global__ void k_cheb_first(int64_t n, T *__restrict__ x, T *__restrict__ r, T *__restrict__ d,
                              const T *__restrict__ tv, T inv_theta, T a, T c, int xz, int last,
                              XDev f) {
@@ -270,7 +321,7 @@ __global__ void k_cheb_first(int64_t n, T *__restrict__ x, T *__restrict__ r, T 
   const T r0 = ldn<NTL>(r + t);
   const T d0 = r0 * inv_theta;
   const T x1 = xz ? d0 : ldn<NTL>(x + t) + d0;
-  const T rn = r0 - read_t<XD>(tv, t, f) * inv_theta;
+  const T rn = r0 - read_t<XD, DI>(tv, t, f) * inv_theta;
   const T dn = a * d0 + c * rn;
   if (last) {
     x[t] = dn + x1;
@@ -280,26 +331,89 @@ __global__ void k_cheb_first(int64_t n, T *__restrict__ x, T *__restrict__ r, T 
     d[t] = dn;
   }
 }
+
+// the last pass of the loop and the closing x += d in one: r and d are not
+// needed afterwards, so only x is written (same roundings as the two passes)
+template <typename T, int XD, bool DI, bool NTL>
+__global__ void k_cheb_last(int64_t n, T *__restrict__ x, const T *__restrict__ r,
+                            const T *__restrict__ d, const T *__restrict__ tv, T a, T c, int xz,
+                            XDev f) {
+  int64_t t = xcd_block() * (int64_t)blockDim.x + threadIdx.x;
+  if (t >= n) return;
+  const T dk = ldn<NTL>(d + t);
+  const T x1 = xz ? dk : ldn<NTL>(x + t) + dk;
+  const T rn = ldn<NTL>(r + t) - read_t<XD, DI>(tv, t, f);
+  const T dn = a * dk + c * rn;
+  stn<NTL>(x + t, dn + x1);
+}
+
+// y = dinv (b - w), w read as above: the Jacobi-smoothed residual
+template <typename T, int XD, bool DI, bool NTL>
+__global__ void k_residual(int64_t n, T *__restrict__ y, const T *__restrict__ b,
+                           const T *__restrict__ tv, XDev f) {
+  int64_t t = xcd_block() * (int64_t)blockDim.x + threadIdx.x;
+  if (t >= n) return;
+  const T v = b[t] - read_t<XD, false>(tv, t, f);
+  if constexpr (DI)
+    y[t] = reinterpret_cast<const T *>(f.di)[within(t, f.vside)] * v;
+  else
+    y[t] = v;
+}
+
+// The form of an update for its vectors: kAll entry by entry, else 16-byte vectors
+// where every operand allows them (kXY needs that), else entry by entry.
+template <typename T, typename Launch>
+static void cheb_dispatch(int64_t n, const XDefer &xd, std::initializer_list<const void *> ps,
+                          Launch &&go) {
+  using VT = typename V16<T>::type;
+  constexpr int W = 16 / sizeof(T);
+  using std::integral_constant;
+  auto with = [&](auto one, auto mode, auto nt, int64_t m, const XDev &f) {
+    if (xd.dinv)
+      go(one, mode, std::true_type{}, nt, m, f);
+    else
+      go(one, mode, std::false_type{}, nt, m, f);
+  };
+  const bool vec = vec16_ok<T>(n, ps) && (!xd.dinv || (aligned16(xd.dinv) && xd.nloc % W == 0));
+  if (xd.on && xd.all) {
+    with(T{}, integral_constant<int, kAll>{}, std::false_type{}, n, xdev<T>(xd, 1));
+  } else if (xd.on) {
+    if (!vec) fail(SEM_EINVAL, "deferred x step needs the vector form");
+    if (cheb_streams<T>(n))
+      with(VT{}, integral_constant<int, kXY>{}, std::true_type{}, n / W, xdev<T>(xd));
+    else
+      with(VT{}, integral_constant<int, kXY>{}, std::false_type{}, n / W, xdev<T>(xd));
+  } else if (vec) {
+    with(VT{}, integral_constant<int, kAsIs>{}, std::false_type{}, n / W, xdev<T>(xd));
+  } else {
+    with(T{}, integral_constant<int, kAsIs>{}, std::false_type{}, n, xdev<T>(xd, 1));
+  }
+}
+
+template <typename T>
+void launch_cheb_update(int64_t n, T *x, T *r, T *d, const T *t, T a, T c, hipStream_t s,
+                        bool x_zero, const XDefer &xd) {
+  cheb_dispatch<T>(n, xd, {x, r, d, t}, [&](auto one, auto mode, auto di, auto nt, int64_t m, XDev f) {
+    using V = decltype(one);
+    hipLaunchKernelGGL((k_cheb_update<V, mode.value, di.value, nt.value>), dim3(nb(m, 256)), dim3(256),
+                       0, s, m, (V *)x, (V *)r, (V *)d, (const V *)t, (V)a, (V)c, (int)x_zero, f);
+  });
+  SEM_LAUNCH("k_cheb_update");
+}
+template void launch_cheb_update<double>(int64_t, double *, double *, double *, const double *,
+                                         double, double, hipStream_t, bool, const XDefer &);
+template void launch_cheb_update<float>(int64_t, float *, float *, float *, const float *, float,
+                                        float, hipStream_t, bool, const XDefer &);
+
 template <typename T>
 void launch_cheb_first(int64_t n, T *x, T *r, T *d, const T *t, T inv_theta, T a, T c,
                        bool x_zero, bool last, hipStream_t s, const XDefer &xd) {
-  const XDev f = xdev<T>(xd);
-  if (vec16_ok<T>(n, {x, r, d, t})) {
-    using VT = typename V16<T>::type;
-    const int64_t m = n / (int64_t)(16 / sizeof(T));
-    if (xd.on)  // r and x streamed non-temporally
-      hipLaunchKernelGGL((k_cheb_first<VT, std::true_type, true>), dim3(nb(m, 256)), dim3(256), 0,
-                         s, m, (VT *)x, (VT *)r, (VT *)d, (const VT *)t, (VT)inv_theta, (VT)a,
-                         (VT)c, (int)x_zero, (int)last, f);
-    else
-      hipLaunchKernelGGL((k_cheb_first<VT>), dim3(nb(m, 256)), dim3(256), 0, s, m, (VT *)x,
-                         (VT *)r, (VT *)d, (const VT *)t, (VT)inv_theta, (VT)a, (VT)c,
-                         (int)x_zero, (int)last, f);
-  } else {
-    if (xd.on) fail(SEM_EINVAL, "deferred x step needs the vector form");
-    hipLaunchKernelGGL((k_cheb_first<T>), dim3(nb(n, 256)), dim3(256), 0, s, n, x, r, d, t,
-                       inv_theta, a, c, (int)x_zero, (int)last, f);
-  }
+  cheb_dispatch<T>(n, xd, {x, r, d, t}, [&](auto one, auto mode, auto di, auto nt, int64_t m, XDev f) {
+    using V = decltype(one);
+    hipLaunchKernelGGL((k_cheb_first<V, mode.value, di.value, nt.value>), dim3(nb(m, 256)), dim3(256),
+                       0, s, m, (V *)x, (V *)r, (V *)d, (const V *)t, (V)inv_theta, (V)a, (V)c,
+                       (int)x_zero, (int)last, f);
+  });
   SEM_LAUNCH("k_cheb_first");
 }
 template void launch_cheb_first<double>(int64_t, double *, double *, double *, const double *,
@@ -308,40 +422,15 @@ template void launch_cheb_first<double>(int64_t, double *, double *, double *, c
 template void launch_cheb_first<float>(int64_t, float *, float *, float *, const float *, float,
                                        float, float, bool, bool, hipStream_t, const XDefer &);
 
-// the last pass of the loop and the closing x += d in one: r and d are not
-// needed afterwards, so only x is written (same roundings as the two passes)
-template <typename T, typename XD = std::false_type, bool NTL = false, bool NTS = false>
-__global__ void k_cheb_last(int64_t n, T *__restrict__ x, const T *__restrict__ r,
-                            const T *__restrict__ d, const T *__restrict__ tv, T a, T c, int xz,
-                            XDev f) {
-  int64_t t = xcd_block() * (int64_t)blockDim.x + threadIdx.x;
-  if (t >= n) return;
-  const T dk = ldn<NTL>(d + t);
-  const T x1 = xz ? dk : ldn<NTL>(x + t) + dk;
-  const T rn = ldn<NTL>(r + t) - read_t<XD>(tv, t, f);
-  const T dn = a * dk + c * rn;
-  stn<NTS>(x + t, dn + x1);
-}
 template <typename T>
 void launch_cheb_last(int64_t n, T *x, const T *r, const T *d, const T *t, T a, T c, hipStream_t s,
                       bool x_zero, const XDefer &xd) {
-  const XDev f = xdev<T>(xd);
-  if (vec16_ok<T>(n, {x, r, d, t})) {
-    using VT = typename V16<T>::type;
-    const int64_t m = n / (int64_t)(16 / sizeof(T));
-    if (xd.on)  // d, x, r and the new x streamed non-temporally
-      hipLaunchKernelGGL((k_cheb_last<VT, std::true_type, true, true>), dim3(nb(m, 256)),
-                         dim3(256), 0, s, m, (VT *)x, (const VT *)r, (const VT *)d, (const VT *)t,
-                         (VT)a, (VT)c, (int)x_zero, f);
-    else
-      hipLaunchKernelGGL((k_cheb_last<VT>), dim3(nb(m, 256)), dim3(256), 0, s, m, (VT *)x,
-                         (const VT *)r, (const VT *)d, (const VT *)t, (VT)a, (VT)c, (int)x_zero,
-                         f);
-  } else {
-    if (xd.on) fail(SEM_EINVAL, "deferred x step needs the vector form");
-    hipLaunchKernelGGL((k_cheb_last<T>), dim3(nb(n, 256)), dim3(256), 0, s, n, x, r, d, t, a, c,
+  cheb_dispatch<T>(n, xd, {x, r, d, t}, [&](auto one, auto mode, auto di, auto nt, int64_t m, XDev f) {
+    using V = decltype(one);
+    hipLaunchKernelGGL((k_cheb_last<V, mode.value, di.value, nt.value>), dim3(nb(m, 256)), dim3(256),
+                       0, s, m, (V *)x, (const V *)r, (const V *)d, (const V *)t, (V)a, (V)c,
                        (int)x_zero, f);
-  }
+  });
   SEM_LAUNCH("k_cheb_last");
 }
 template void launch_cheb_last<double>(int64_t, double *, const double *, const double *,
@@ -350,6 +439,20 @@ template void launch_cheb_last<double>(int64_t, double *, const double *, const 
 template void launch_cheb_last<float>(int64_t, float *, const float *, const float *,
                                       const float *, float, float, hipStream_t, bool,
                                       const XDefer &);
+
+template <typename T>
+void launch_residual(int64_t n, T *y, const T *b, const T *w, hipStream_t s, const XDefer &xd) {
+  cheb_dispatch<T>(n, xd, {y, b, w}, [&](auto one, auto mode, auto di, auto nt, int64_t m, XDev f) {
+    using V = decltype(one);
+    hipLaunchKernelGGL((k_residual<V, mode.value, di.value, false>), dim3(nb(m, 256)), dim3(256), 0, s,
+                       m, (V *)y, (const V *)b, (const V *)w, f);
+  });
+  SEM_LAUNCH("k_residual");
+}
+template void launch_residual<double>(int64_t, double *, const double *, const double *, hipStream_t,
+                                      const XDefer &);
+template void launch_residual<float>(int64_t, float *, const float *, const float *, hipStream_t,
+                                     const XDefer &);
 
 __global__ void k_jacobi_inv(int64_t n, const double *__restrict__ diag, const double *__restrict__ w,
                              double *__restrict__ dinv, float *__restrict__ dinv32) {
@@ -619,7 +722,7 @@ __global__ __launch_bounds__(256) void k_fcg_xr(int64_t n, const double *__restr
     double2 qv;
     if constexpr (XD::value) {
       using VT = typename V16<double>::type;
-      const VT qq = read_t<XD>(reinterpret_cast<const VT *>(q), t, f);
+      const VT qq = read_xy(reinterpret_cast<const VT *>(q), t, f);
       qv = make_double2(qq[0], qq[1]);
     } else {
       qv = ld2<V>(q, t);

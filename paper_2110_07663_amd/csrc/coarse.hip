@@ -730,9 +730,9 @@ static void ensure_graph(Ctx &c) {
   SEM_HIP(hipGraphInstantiate(&S.exec, S.graph, nullptr, nullptr, 0));
 }
 
-// one right side: bl (consistent, masked E-vector of the coarsest level) -> xl
+// one right side: bl (consistent, masked E-vector of the coarsest level) -> S.x
 static void coarse_solve_one(Ctx &c, Level &C, double tol, int maxit, hipStream_t s,
-                             const double *bl, double *xl, CoarseRhs u) {
+                             const double *bl, CoarseRhs u) {
   CoarseSolver &S = *c.cs;
   CoarseGrid g = cgrid(c);
   CgPtrs P = ptrs(c);
@@ -754,7 +754,6 @@ static void coarse_solve_one(Ctx &c, Level &C, double tol, int maxit, hipStream_
     if (h->aborted) fail(SEM_EHIP, "coarse-grid solve: a grid barrier timed out");
     c.last_coarse_iters = tol > 0.0 ? h->iters : maxit;
     if (!(h->rr == h->rr)) fail(SEM_ENAN, "NaN in the coarse-grid solve");
-    launch_gather(c, C, S.x, xl, s);
     return;
   }
   hipLaunchKernelGGL(k_cg_start, dim3(cg_grid(S)), dim3(256), 0, s, S.n, P,
@@ -766,7 +765,6 @@ static void coarse_solve_one(Ctx &c, Level &C, double tol, int maxit, hipStream_
     // inside a recorded batch iteration: a fixed count, no readback
     const int k = tol > 0.0 ? std::min(maxit, c.capture_coarse_iters) : maxit;
     enqueue_iterations(c, k, 0, s);
-    launch_gather(c, C, S.x, xl, s);
     return;
   }
   if (tol <= 0.0 || !S.use_graph) {
@@ -809,28 +807,34 @@ static void coarse_solve_one(Ctx &c, Level &C, double tol, int maxit, hipStream_
   if (tol > 0.0) c.last_coarse_iters = h->iters;
   else c.last_coarse_iters = maxit;
   if (!(h->rr == h->rr)) fail(SEM_ENAN, "NaN in the coarse-grid solve");
-  launch_gather(c, C, S.x, xl, s);
 }
 
 // solve on the coarsest level for nv right sides: C.d_b (consistent, masked
-// E-vectors, nloc apart) -> c.cx.  The exact solve takes all right sides in one
+// E-vectors, nloc apart) -> x (or xf).  The exact solve takes all right sides in one
 // pair of sweeps; the iterative one solves them in turn.
 void coarse_solve_assembled(Ctx &c, Level &C, double tol, int maxit, hipStream_t s, int nv,
-                            CoarseRhs u) {
+                            CoarseRhs u, double *x, float *xf) {
   CoarseSolver &S = *c.cs;
   if (nv > c.nvmax) fail(SEM_EINVAL, "coarse solve: more right sides than were set up");
+  auto out = [&](int v, int k) {  // right sides v .. v + k - 1 of the E-vectors from S.x
+    if (xf)
+      launch_gather(c, C, S.x, xf + v * C.nloc, s, k, S.n);
+    else
+      launch_gather(c, C, S.x, x + v * C.nloc, s, k, S.n);
+  };
   if (S.direct) {  // exact: no iteration, no host interaction (also inside a recorded graph)
     CoarseGrid g = cgrid(c);
     launch_to_global(S, g, C.d_b, u, nv, s);
     coarse_direct_apply(S, S.b, S.x, s, nv);
     if (!c.capturing) c.last_coarse_iters = 0;
-    launch_gather(c, C, S.x, c.cx, s, nv, S.n);
+    out(0, nv);
     return;
   }
   for (int v = 0; v < nv; ++v) {
     CoarseRhs uv = u;
     if (u.p) uv.p = (const char *)u.p + (size_t)v * C.nloc * (u.f32 ? sizeof(float) : sizeof(double));
-    coarse_solve_one(c, C, tol, maxit, s, C.d_b + v * C.nloc, c.cx + v * C.nloc, uv);
+    coarse_solve_one(c, C, tol, maxit, s, C.d_b + v * C.nloc, uv);
+    out(v, 1);
   }
 }
 

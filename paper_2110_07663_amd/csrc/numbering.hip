@@ -169,15 +169,16 @@ __global__ void k_fill1(int64_t n, double *w64, float *w32) {
   if (w32) w32[t] = 1.0f;
 }
 
+template <typename T>
 __global__ void k_gather(GridInfo g, int64_t nloc, const double *__restrict__ ug,
-                         double *__restrict__ ul, int64_t ug_stride) {
+                         T *__restrict__ ul, int64_t ug_stride) {
   int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (t >= nloc) return;
   ug += blockIdx.y * ug_stride;  // right side blockIdx.y
   ul += blockIdx.y * nloc;
   int64_t gx, gy, gz;
   global_coords(g, t, gx, gy, gz);
-  ul[t] = ug[(gz * g.ny + gy) * g.nx + gx];
+  ul[t] = (T)ug[(gz * g.ny + gy) * g.nx + gx];
 }
 
 // SplitMix64 (Steele, Lea & Flood 2014) of (seed XOR gid), top 53 bits -> [-1, 1)
@@ -633,13 +634,18 @@ void launch_weights(const Level &L, hipStream_t s) {
   SEM_LAUNCH("k_weights");
 }
 
-void launch_gather(const Ctx &c, const Level &L, const double *ug, double *ul, hipStream_t s,
+template <typename T>
+void launch_gather(const Ctx &c, const Level &L, const double *ug, T *ul, hipStream_t s,
                    int nv, int64_t ug_stride) {
   GridInfo g = grid_of(c, L);
-  hipLaunchKernelGGL(k_gather, dim3(nb(L.nloc, 256), (unsigned)nv), dim3(256), 0, s, g, L.nloc,
+  hipLaunchKernelGGL(k_gather<T>, dim3(nb(L.nloc, 256), (unsigned)nv), dim3(256), 0, s, g, L.nloc,
                      ug, ul, ug_stride);
   SEM_LAUNCH("k_gather");
 }
+template void launch_gather<double>(const Ctx &, const Level &, const double *, double *,
+                                    hipStream_t, int, int64_t);
+template void launch_gather<float>(const Ctx &, const Level &, const double *, float *,
+                                   hipStream_t, int, int64_t);
 
 void launch_start_vector(const Ctx &c, const Level &L, uint64_t seed, double *v, hipStream_t s) {
   GridInfo g = grid_of(c, L);

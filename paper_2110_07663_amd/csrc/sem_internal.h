@@ -112,6 +112,7 @@ struct Level {
   int gs_all = -1;                   // all passes in one launch: 1 yes, 0 no, -1 small levels only
   bool xdefer = true;                // Chebyshev updates may take the x step of S's gather-scatter
   bool ydefer = true;                // ... and its y step
+  bool zdefer = true;                // ... and every step on small levels
   double *dotpart = nullptr;         // [E] element shares of (p, Ap) (finest level)
 
   // 1D operators (device): GLL nodes/weights, derivative matrix D[i][j] = h_j'(xi_i)
@@ -301,7 +302,8 @@ void launch_rhs(const Level &L, const double *f, double *b, hipStream_t s);
 // numbering.hip
 size_t gs_sort_temp_bytes(int64_t nloc);
 void build_gather_scatter(const Ctx &c, Level &L, Arena &scratch, hipStream_t s);
-void launch_gather(const Ctx &c, const Level &L, const double *ug, double *ul, hipStream_t s,
+template <typename T>
+void launch_gather(const Ctx &c, const Level &L, const double *ug, T *ul, hipStream_t s,
                    int nv = 1, int64_t ug_stride = 0);
 // nv > 1: nv vectors nloc apart (several right sides of one problem)
 // x_in_blocks: the x-faces inside each group of 4 elements along x are summed
@@ -331,24 +333,32 @@ void launch_diag(const Level &L, double *d, hipStream_t s);
 
 // blas.hip
 template <typename T>
-void launch_scale(int64_t n, const T *w, const T *x, T *y, hipStream_t s);  // y = w.*x
+void launch_scale(int64_t n, const T *w, const T *x, T *y, hipStream_t s,  // y = w.*x
+                  int nv = 1);  // nv vectors x, y n apart, one w
 void launch_copy_cvt_d2f(int64_t n, const double *x, float *y, hipStream_t s);
 void launch_copy_cvt_f2d(int64_t n, const float *x, double *y, hipStream_t s);
 template <typename T>
 void launch_axpby(int64_t n, T a, const T *x, T b, T *y, hipStream_t s);  // y = a x + b y
 template <typename T>
 void launch_sub(int64_t n, const T *a, const T *b, T *y, hipStream_t s);  // y = a - b
-// The x step of the gather-scatter left to the Chebyshev update that reads t
-// (the y and z passes done): each copy on an x-face adds its neighbour's copy
-// as it reads, (p-face + 0-face), and the Dirichlet x-faces read as zero.
-// on = false: t is assembled already.
+// Steps of the gather-scatter left to the Chebyshev update that reads t: the x
+// step (the y and z passes done): each copy on an x-face adds its neighbour's copy
+// as it reads, (p-face + 0-face), and the Dirichlet x-faces read as zero; with y
+// the y step too (the gather-scatter ran its z pass only); with all every step
+// (no gather-scatter ran).  on = false: t is assembled already.
+// dinv: t is dinv times what is read (Jacobi smoothing of A's output).
 struct XDefer {
   bool on = false;
   int nex = 0, N = 0, bc0 = 0, bc1 = 0;
   int64_t nloc = 0;  // right sides nloc apart
-  bool y = false;    // the y step too (the gather-scatter ran its z pass only)
+  bool y = false;
   int ney = 0, bc2 = 0, bc3 = 0;
+  bool all = false;
+  int nez = 0, bc4 = 0, bc5 = 0;
+  const void *dinv = nullptr;
 };
+// the deferred steps of a level (on, and the grid the readers need)
+XDefer xdefer_of(const Level &L, bool y, bool all);
 // whether launch_cheb_* can take the x step for these vectors (16-byte
 // vectors that do not straddle the element rows)
 template <typename T>
@@ -365,6 +375,9 @@ void launch_cheb_last(int64_t n, T *x, const T *r, const T *d, const T *t, T a, 
 template <typename T>
 void launch_cheb_first(int64_t n, T *x, T *r, T *d, const T *t, T inv_theta, T a, T c,
                        bool x_zero, bool last, hipStream_t s, const XDefer &xd = XDefer());
+// y = b - w, times xd.dinv when given; w as the updates read t
+template <typename T>
+void launch_residual(int64_t n, T *y, const T *b, const T *w, hipStream_t s, const XDefer &xd);
 void launch_jacobi_inv(int64_t n, const double *diag, const double *w, double *dinv, float *dinv32,
                        hipStream_t s);
 // weighted dots: out[j] = sum_i w_i a_j(i) b_j(i), j < nd <= 4 (fixed-order reduction)
@@ -454,8 +467,9 @@ struct CoarseRhs {
   const void *p = nullptr;
   bool f32 = false;
 };
-void coarse_solve_assembled(Ctx &c, Level &C, double tol, int maxit, hipStream_t s, int nv = 1,
-                            CoarseRhs u = {});
+// xf (may be null): the solution goes there in FP32 instead of to c.cx
+void coarse_solve_assembled(Ctx &c, Level &C, double tol, int maxit, hipStream_t s, int nv,
+                            CoarseRhs u, double *x, float *xf);
 void coarse_release(CoarseSolver &S);
 BtShape coarse_direct_shape(int64_t nx, int64_t ny, int64_t nz, bool f32);
 void coarse_direct_setup(CoarseSolver &S, int64_t nx, int64_t ny, int64_t nz, hipStream_t s);

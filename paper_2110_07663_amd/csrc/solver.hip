@@ -337,6 +337,9 @@ static void init_ctx(Ctx &c, const sem_mesh *m, int p, const int8_t *bc, const s
       // SEM_GS_YDEFER=0: ... its x step only (y and z passes run)
       const char *ydv = getenv("SEM_GS_YDEFER");
       L.ydefer = !(ydv && ydv[0] == '0');
+      // SEM_GS_ZDEFER=0: the updates of small levels read assembled vectors
+      const char *zdv = getenv("SEM_GS_ZDEFER");
+      L.zdefer = !(zdv && zdv[0] == '0');
       // SEM_GS_YZ=0 / 1: the y and z passes as two launches / one launch in
       // both precisions (default: one launch for FP64, measured faster there
       // and slower in FP32)
@@ -482,16 +485,7 @@ static void opA_dot(const Ctx &c, const Level &L, const double *p, double *q, do
         ProfScope ps(c, L, SEM_PROF_GS64, s);
         launch_gs<double>(L, q, s, 1, false, true, true);
       }
-      xq->on = true;
-      xq->nex = L.nex;
-      xq->N = L.N;
-      xq->bc0 = L.bc[0];
-      xq->bc1 = L.bc[1];
-      xq->nloc = L.nloc;
-      xq->y = true;
-      xq->ney = L.ney;
-      xq->bc2 = L.bc[2];
-      xq->bc3 = L.bc[3];
+      *xq = xdefer_of(L, true, false);
     } else {
       opA<double>(c, L, p, q, s, 1, L.dotpart);
     }
@@ -501,6 +495,33 @@ static void opA_dot(const Ctx &c, const Level &L, const double *p, double *q, do
   opA<double>(c, L, p, q, s);
   const double *a[1] = {p}, *bb[1] = {q};
   launch_wdots(c, L.nloc, L.w64, 1, a, bb, pq, s, L.w32);
+}
+
+XDefer xdefer_of(const Level &L, bool y, bool all) {
+  XDefer xd;
+  xd.on = true;
+  xd.nex = L.nex;
+  xd.ney = L.ney;
+  xd.nez = L.nez;
+  xd.N = L.N;
+  xd.nloc = L.nloc;
+  xd.y = y;
+  xd.all = all;
+  xd.bc0 = L.bc[0];
+  xd.bc1 = L.bc[1];
+  xd.bc2 = L.bc[2];
+  xd.bc3 = L.bc[3];
+  xd.bc4 = L.bc[4];
+  xd.bc5 = L.bc[5];
+  return xd;
+}
+
+// Whether the Chebyshev updates of this level sum all copies of a node as they
+// read A's or S's output, with no gather-scatter before them: where that would
+// be one launch of a level whose time is its launches (gs_in_one_launch).
+template <typename T>
+static bool update_takes_all(const Level &L, int nv) {
+  return L.xdefer && L.ydefer && L.zdefer && gs_in_one_launch(L, sizeof(T), nv);
 }
 
 // rs (may be null): apply S to r - rs; r - rs is formed as the VALU FDM reads
@@ -575,14 +596,15 @@ static void opS(const Ctx &c, const Level &L, const T *r, T *z, hipStream_t s, i
   if (!schwarz) {
     const T *dinv = Vec<T>::dinv(L);
     if (!dinv) fail(SEM_EINVAL, "Jacobi data of this precision were not built");
-    for (int k = 0; k < nv; ++k) launch_scale<T>(L.nloc, dinv, r + k * L.nloc, z + k * L.nloc, s);
+    launch_scale<T>(L.nloc, dinv, r, z, s, nv);
     return;
   }
   // S's output may leave the x step of its gather-scatter to a reader (xd),
   // or arrive with the x-faces inside each FDM workgroup summed
-  const bool defer = !asm_mode && xd && L.gs_struct && L.xdefer &&
+  const bool all = !asm_mode && xd && update_takes_all<T>(L, nv);
+  const bool defer = !asm_mode && !all && xd && L.gs_struct && L.xdefer &&
                      cheb_can_defer_x<T>(L.N, L.nloc * nv, {z});
-  const bool fxf = !asm_mode && !defer && !mfma && (xin & 3) != 1 && fdm_sums_x_faces<T>(c, L, nv);
+  const bool fxf = !asm_mode && !all && !defer && !mfma && (xin & 3) != 1 && fdm_sums_x_faces<T>(c, L, nv);
   {
     ProfScope ps(c, L, SEM_PROF_FDM, s);
     if constexpr (sizeof(T) == 4) {
@@ -594,18 +616,11 @@ static void opS(const Ctx &c, const Level &L, const T *r, T *z, hipStream_t s, i
     if (!mfma && !mf16) launch_fdm<T>(c, L, r, z, asm_mode, s, nv, rs, xin | (fxf ? 8 : 0));
   }
   if (asm_mode) return;  // the overlap sum already produced a consistent, masked vector
-  if (defer) {
-    xd->on = true;
-    xd->nex = L.nex;
-    xd->N = L.N;
-    xd->bc0 = L.bc[0];
-    xd->bc1 = L.bc[1];
-    xd->nloc = L.nloc;
-    xd->y = L.ydefer;
-    xd->ney = L.ney;
-    xd->bc2 = L.bc[2];
-    xd->bc3 = L.bc[3];
+  if (all) {  // no gather-scatter: the update sums the copies as it reads
+    *xd = xdefer_of(L, true, true);
+    return;
   }
+  if (defer) *xd = xdefer_of(L, L.ydefer, false);
   ProfScope ps(c, L, sizeof(T) == 8 ? SEM_PROF_GS64 : SEM_PROF_GS32, s);
   launch_gs<T>(L, z, s, nv, fxf, defer, defer && L.ydefer);
 }
@@ -614,7 +629,7 @@ static void opS(const Ctx &c, const Level &L, const T *r, T *z, hipStream_t s, i
 template <typename T>
 static void chebyshev(const Ctx &c, Level &L, const T *b, T *x, bool x_zero, hipStream_t s,
                       int nv = 1) {
-  T *r = Vec<T>::r(L), *d = Vec<T>::d(L), *w = Vec<T>::w(L), *t = Vec<T>::t(L);
+  T *r = Vec<T>::r(L), *d = Vec<T>::d(L), *w = Vec<T>::w(L), *z = Vec<T>::t(L);
   const double theta = 0.5 * (L.lmax + L.lmin), delta = 0.5 * (L.lmax - L.lmin);
   const double sigma = theta / delta;
   const int64_t n = L.nloc * nv;  // the vector updates are pointwise over all right sides
@@ -622,8 +637,39 @@ static void chebyshev(const Ctx &c, Level &L, const T *b, T *x, bool x_zero, hip
   // A's output that only feeds S may leave the x step of its gather-scatter to S
   const bool xs = fdm_takes_x_step<T>(c, L);
   const int ys = fdm_takes_y_step<T>(c, L) ? 4 : 0;
+  // Jacobi: S is diagonal and acts on A's output node by node, so the updates
+  // read that output with its deferred steps and scale it on the way
+  const bool jacobi = c.opts.smoother == SEM_SMOOTH_JACOBI;
+  const T *dinv = Vec<T>::dinv(L);
+  if (jacobi && !dinv) fail(SEM_EINVAL, "Jacobi data of this precision were not built");
+  // w = A u up to the steps left to the reader, which the result names
+  auto opA_read = [&](const T *u, std::initializer_list<const void *> ps) {
+    XDefer xd;
+    if (update_takes_all<T>(L, nv)) {
+      xd = xdefer_of(L, true, true);
+      ProfScope pr(c, L, sizeof(T) == 8 ? SEM_PROF_AX64 : SEM_PROF_AX32, s);
+      launch_ax<T>(L, u, w, s, nv, false, nullptr);
+    } else if (L.gs_struct && L.xdefer && L.ydefer && cheb_can_defer_x<T>(L.N, n, ps) &&
+               cheb_can_defer_x<T>(L.N, n, {w, dinv})) {
+      xd = xdefer_of(L, true, false);
+      {
+        ProfScope pr(c, L, sizeof(T) == 8 ? SEM_PROF_AX64 : SEM_PROF_AX32, s);
+        launch_ax<T>(L, u, w, s, nv, false, nullptr);
+      }
+      ProfScope pr(c, L, sizeof(T) == 8 ? SEM_PROF_GS64 : SEM_PROF_GS32, s);
+      launch_gs<T>(L, w, s, nv, false, true, true);
+    } else {
+      opA<T>(c, L, u, w, s, nv);
+      xd.nloc = L.nloc;
+    }
+    xd.dinv = dinv;
+    return xd;
+  };
   if (x_zero) {
     opS<T>(c, L, b, r, s, nv);
+  } else if (jacobi) {
+    const XDefer xd = opA_read(x, {r, b});
+    launch_residual<T>(n, r, b, w, s, xd);  // r = S (b - A x)
   } else if (xs) {
     opA_nox<T>(c, L, x, w, s, nv);
     opS<T>(c, L, b, r, s, nv, w, nullptr, 2 | ys);  // r = S (b - A x)
@@ -641,13 +687,20 @@ static void chebyshev(const Ctx &c, Level &L, const T *b, T *x, bool x_zero, hip
   // pass 0 works from r_0 itself (d_0 = r_0 / theta is formed inside the update,
   // A and S being linear); a zero start is not written
   for (int k = 0; k < L.K; ++k) {
-    if (xs)
-      opA_nox<T>(c, L, k == 0 ? r : d, w, s, nv);
-    else
-      opA<T>(c, L, k == 0 ? r : d, w, s, nv);
-    XDefer xd;  // t only feeds the update below: it may take the x step itself
-    opS<T>(c, L, w, t, s, nv, nullptr, cheb_can_defer_x<T>(L.N, n, {x, r, d, t}) ? &xd : nullptr,
-           xs ? 1 | ys : 0);
+    XDefer xd;  // t only feeds the update below: it may take gather-scatter steps itself
+    const T *t = w;
+    if (jacobi) {
+      xd = opA_read(k == 0 ? r : d, {x, r, d});
+    } else {
+      if (xs)
+        opA_nox<T>(c, L, k == 0 ? r : d, w, s, nv);
+      else
+        opA<T>(c, L, k == 0 ? r : d, w, s, nv);
+      opS<T>(c, L, w, z, s, nv, nullptr,
+             update_takes_all<T>(L, nv) || cheb_can_defer_x<T>(L.N, n, {x, r, d, z}) ? &xd : nullptr,
+             xs ? 1 | ys : 0);
+      t = z;
+    }
     double rho_new = 1.0 / (2.0 * sigma - rho);
     const T a = (T)(rho_new * rho), cc = (T)(2.0 * rho_new / delta);
     const bool last = k + 1 == L.K;
@@ -666,18 +719,11 @@ static void host_scalars(Ctx &c, const void *dev, size_t bytes, hipStream_t s) {
   SEM_HIP(hipStreamSynchronize(s));
 }
 
-// coarse Jacobi-PCG from x = 0: C.d_b -> c.cx (all scalars on the device);
-// u.p: the right side as the restriction left it (assembled solver only)
-static void coarse_solve(Ctx &c, Level &C, hipStream_t s, int nv = 1, CoarseRhs u = {}) {
+// Jacobi-PCG from x = 0 on the E-vectors of the coarsest level: C.d_b -> c.cx (all
+// scalars on the device)
+static void coarse_pcg(Ctx &c, Level &C, hipStream_t s) {
   const double tol = c.opts.coarse_tol;
   const int maxit = c.opts.coarse_maxit;
-  ProfScope ps(c, C, SEM_PROF_COARSE, s);
-  if (coarse_assembled_ok(c, C)) {
-    coarse_solve_assembled(c, C, tol, maxit, s, nv, u);
-    return;
-  }
-  if (u.p) fail(SEM_EINVAL, "coarse solve: the right side must be assembled");
-  if (nv != 1) fail(SEM_EUNSUPPORTED, "several right sides need the assembled p = 1 coarse solve");
   DevScalars init{};
   init.tol2 = tol * tol;
   init.maxit = maxit;
@@ -712,6 +758,24 @@ static void coarse_solve(Ctx &c, Level &C, hipStream_t s, int nv = 1, CoarseRhs 
   }
 }
 
+// The coarse solve: C.d_b, or u.p as the restriction left it (assembled solver
+// only), to x, or to xf in FP32
+static void coarse_solve(Ctx &c, Level &C, hipStream_t s, int nv, CoarseRhs u, double *x,
+                         float *xf) {
+  ProfScope ps(c, C, SEM_PROF_COARSE, s);
+  if (coarse_assembled_ok(c, C)) {
+    coarse_solve_assembled(c, C, c.opts.coarse_tol, c.opts.coarse_maxit, s, nv, u, x, xf);
+    return;
+  }
+  if (u.p) fail(SEM_EINVAL, "coarse solve: the right side must be assembled");
+  if (nv != 1) fail(SEM_EUNSUPPORTED, "several right sides need the assembled p = 1 coarse solve");
+  coarse_pcg(c, C, s);
+  if (xf)
+    launch_copy_cvt_d2f(C.nloc, c.cx, xf, s);
+  else
+    launch_copy<double>(C.nloc, c.cx, x, s);
+}
+
 // Whether level C's right side may reach the coarse solve as the restriction
 // leaves it: the assembled solver's mapping to its global numbering then sums
 // the copies of each node (no gather-scatter, no FP64 copy on the level)
@@ -726,16 +790,14 @@ static void vcycle_level(Ctx &c, int l, hipStream_t s, int nv = 1, bool unassemb
   Level &L = c.lev[l];
   const int64_t n = L.nloc * nv;
   if (L.coarse) {
-    if (unassembled) {
-      coarse_solve(c, L, s, nv, CoarseRhs{Vec<T>::b(L), sizeof(T) == 4});
+    CoarseRhs u;
+    if (unassembled) u = CoarseRhs{Vec<T>::b(L), sizeof(T) == 4};
+    if constexpr (sizeof(T) == 4) {
+      if (!unassembled) launch_copy_cvt_f2d(n, L.f_b, L.d_b, s);
+      coarse_solve(c, L, s, nv, u, nullptr, L.f_x);
     } else {
-      if constexpr (sizeof(T) == 4) launch_copy_cvt_f2d(n, L.f_b, L.d_b, s);
-      coarse_solve(c, L, s, nv);
+      coarse_solve(c, L, s, nv, u, L.d_x, nullptr);
     }
-    if constexpr (sizeof(T) == 4)
-      launch_copy_cvt_d2f(n, c.cx, L.f_x, s);
-    else
-      launch_copy<double>(n, c.cx, L.d_x, s);
     return;
   }
   Level &C = c.lev[l + 1];
@@ -765,14 +827,12 @@ static void precondition(Ctx &c, const double *r, double *z, hipStream_t s, int 
   if (nv < 1 || nv > c.nvmax) fail(SEM_EINVAL, "preconditioner: more right sides than were set up");
   const int64_t n = F.nloc * nv;
   if (c.opts.precond == SEM_PRECOND_JACOBI) {
-    for (int k = 0; k < nv; ++k)
-      launch_scale<double>(F.nloc, F.dinv64, r + k * F.nloc, z + k * F.nloc, s);
+    launch_scale<double>(F.nloc, F.dinv64, r, z, s, nv);
     return;
   }
   if (F.coarse) {  // single-level schedule: the coarse solve itself, on FP64 vectors
     launch_copy<double>(n, r, F.d_b, s);
-    coarse_solve(c, F, s, nv);
-    launch_copy<double>(n, c.cx, z, s);
+    coarse_solve(c, F, s, nv, CoarseRhs{}, z, nullptr);
     return;
   }
   if (c.lowp) {
@@ -780,9 +840,27 @@ static void precondition(Ctx &c, const double *r, double *z, hipStream_t s, int 
     vcycle_level<float>(c, 0, s, nv);
     launch_copy_cvt_f2d(n, F.f_x, z, s);
   } else {
-    launch_copy<double>(n, r, F.d_b, s);
+    // The V-cycle reads r and forms x in z themselves where their alignment suits
+    // its 16-byte accesses and they do not overlap (r is only read); else in
+    // the level's own vectors, with two copies.
+    const bool direct = ((uintptr_t)r & 15) == 0 && ((uintptr_t)z & 15) == 0 && (r + n <= z || z + n <= r);
+    if (!direct) {
+      launch_copy<double>(n, r, F.d_b, s);
+      vcycle_level<double>(c, 0, s, nv);
+      launch_copy<double>(n, F.d_x, z, s);
+      return;
+    }
+    struct Borrow {  // for this call only
+      Level &L;
+      double *b, *x;
+      ~Borrow() {
+        L.d_b = b;
+        L.d_x = x;
+      }
+    } borrow{F, F.d_b, F.d_x};
+    F.d_b = const_cast<double *>(r);
+    F.d_x = z;
     vcycle_level<double>(c, 0, s, nv);
-    launch_copy<double>(n, F.d_x, z, s);
   }
 }
 
