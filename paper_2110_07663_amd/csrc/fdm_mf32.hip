@@ -158,7 +158,8 @@ struct Mf {
   static constexpr int UF = (QF + 15) / 16, UB = (QB + 15) / 16;
   static constexpr int NLY = PB * NK, SY = (NLY + 63) / 64;  // backward y lines (kept planes)
   static constexpr int NLX = NK * NK, SX = (NLX + 63) / 64;  // backward x lines (kept rows)
-  static constexpr int BUF = NL * LS;                        // floats per wavefront
+  // floats per wavefront (the last exchange spaces its planes by NK + 1 lines)
+  static constexpr int NLB = NK * (NK + 1) > NL ? NK * (NK + 1) : NL, BUF = NLB * LS;
   static constexpr int WAVES = 4;
   // 16-bit operands: k in groups of four (forward: the line's nodes; backward:
   // the modes), one register pair of A operands per direction and pass kind
@@ -196,6 +197,17 @@ struct BufF32 {
   }
 };
 
+// Issue priorities of a wave: lowest while it issues a contraction's products,
+// higher after it, highest once it exchanges lines through LDS.  The 6 waves of a
+// SIMD otherwise drift into the same phase and the matrix pipe and the LDS take
+// turns (the kernel without its loads, p = 7, 32^3: 74 us, without its products 43,
+// with both 75); with the priorities a wave between two contractions overtakes
+// those inside one.  Measured at 32^3, p = 7, FP32: 74.8 -> 64.9 us with assembled
+// input (with the line order of the last exchange, below, 4 of them); raising the
+// products instead gives the same there, but 92.2 against 90.2 us on average over
+// the three forms of a smoothing step (101.4 before).
+constexpr int kPrioMatrix = 0, kPrioMove = 2, kPrioLds = 3;
+
 // forward contraction of one slot: acc[g][i] = sum_k v[k] S[k][4g + i]
 template <int P>
 __device__ __attribute__((always_inline)) inline void mf_forward(const float *A, const float *v,
@@ -203,6 +215,7 @@ __device__ __attribute__((always_inline)) inline void mf_forward(const float *A,
   using F = Mf<P>;
 #pragma unroll
   for (int g = 0; g < F::MG; ++g) acc[g] = mf4_t{0.f, 0.f, 0.f, 0.f};
+  __builtin_amdgcn_s_setprio(kPrioMatrix);
 #pragma unroll
   for (int k = 0; k < F::PB; ++k)
 #pragma unroll
@@ -210,6 +223,7 @@ __device__ __attribute__((always_inline)) inline void mf_forward(const float *A,
       const int q = k * F::MG + g;
       acc[g] = mfma_bq(A[q >> 4], v[k], acc[g], q & 15);
     }
+  __builtin_amdgcn_s_setprio(kPrioMove);
 }
 
 // backward contraction to the kept nodes: acc[g][i] = sum_m S[K0 + 4g + i][m] h[m]
@@ -219,6 +233,7 @@ __device__ __attribute__((always_inline)) inline void mf_backward(const float *A
   using F = Mf<P, AS>;
 #pragma unroll
   for (int g = 0; g < F::KG; ++g) acc[g] = mf4_t{0.f, 0.f, 0.f, 0.f};
+  __builtin_amdgcn_s_setprio(kPrioMatrix);
 #pragma unroll
   for (int m = 0; m < F::PB; ++m)
 #pragma unroll
@@ -226,6 +241,7 @@ __device__ __attribute__((always_inline)) inline void mf_backward(const float *A
       const int q = m * F::KG + g;
       acc[g] = mfma_bq(A[q >> 4], h[m], acc[g], q & 15);
     }
+  __builtin_amdgcn_s_setprio(kPrioMove);
 }
 
 // the 16-bit forms of the two contractions: the B operands are the line's
@@ -247,10 +263,12 @@ __device__ __attribute__((always_inline)) inline void mf16_forward(u2_t A, const
   mf16_operands<P, OP, SC>(v, sc, b);
 #pragma unroll
   for (int g = 0; g < F::MG; ++g) acc[g] = mf4_t{0.f, 0.f, 0.f, 0.f};
+  __builtin_amdgcn_s_setprio(kPrioMatrix);
 #pragma unroll
   for (int kg = 0; kg < F::K4; ++kg)
 #pragma unroll
     for (int g = 0; g < F::MG; ++g) acc[g] = mfma16<OP>(A, b[kg], acc[g], kg * F::MG + g);
+  __builtin_amdgcn_s_setprio(kPrioMove);
 }
 template <int P, int OP, bool SC>
 __device__ __attribute__((always_inline)) inline void mf16_backward(u2_t A, const float *h,
@@ -260,10 +278,12 @@ __device__ __attribute__((always_inline)) inline void mf16_backward(u2_t A, cons
   mf16_operands<P, OP, SC>(h, sc, b);
 #pragma unroll
   for (int g = 0; g < F::KG; ++g) acc[g] = mf4_t{0.f, 0.f, 0.f, 0.f};
+  __builtin_amdgcn_s_setprio(kPrioMatrix);
 #pragma unroll
   for (int mg = 0; mg < F::K4; ++mg)
 #pragma unroll
     for (int g = 0; g < F::KG; ++g) acc[g] = mfma16<OP>(A, b[mg], acc[g], mg * F::KG + g);
+  __builtin_amdgcn_s_setprio(kPrioMove);
 }
 
 template <int P>
@@ -283,6 +303,7 @@ __device__ __attribute__((always_inline)) inline void mf_read_line(const float *
 // orders the LDS traffic of one wavefront between passes (global loads in
 // flight, such as the next element's box, are not waited for)
 __device__ inline void mf_sync() {
+  __builtin_amdgcn_s_setprio(kPrioLds);
   __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0) only
   __builtin_amdgcn_wave_barrier();
 }
@@ -728,7 +749,9 @@ __device__ __attribute__((always_inline)) inline void mf_solve(
   }
   mf_sync();
 
-  // back along y: line (a', k) -> kept rows j = 1..N, written as x-lines (j, k), position a'
+  // back along y: line (a', k) -> kept rows j = 1..N, written as x-lines (j, k),
+  // position a'.  NK + 1 lines per plane k: at NK = 8 the planes of a write would
+  // otherwise all start on the same bank.
   float w[F::SY][PB];
   mf4_t by[F::SY][KG];
 #pragma unroll
@@ -753,7 +776,7 @@ __device__ __attribute__((always_inline)) inline void mf_solve(
       for (int g = 0; g < KG; ++g)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          if (4 * g + i < NK) buf[(4 * g + i + NK * k) * LS + a] = by[s][g][i];
+          if (4 * g + i < NK) buf[(4 * g + i + (NK + 1) * k) * LS + a] = by[s][g][i];
     }
   }
   mf_sync();
@@ -771,7 +794,8 @@ __device__ __attribute__((always_inline)) inline void mf_solve(
     const int l = 64 * s + lane;
     float u[PB];
     mf4_t bx[KG];
-    mf_read_line<P>(buf, l < F::NLX ? l : 0, u);
+    const int lr = l < F::NLX ? l : 0;
+    mf_read_line<P>(buf, lr + lr / NK, u);  // line j + (NK + 1) k
     if constexpr (OP != kOpF32) {
       mf16_backward<P, OP, false>(lt.Ab16[0], u, 1.f, bx);
 #pragma unroll
