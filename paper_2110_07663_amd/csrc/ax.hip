@@ -200,8 +200,8 @@ __device__ __forceinline__ void st(T *p, T v) {
   else *p = v;
 }
 
-// XF: the four elements of a workgroup are consecutive along x (nex a multiple
-// of 4), and the copies on their three shared x-faces are summed here, in LDS,
+// XF > 0: the XF (4 or 8) elements of a workgroup are consecutive along x (nex a
+// multiple of XF), and the copies on the x-faces they share are summed here, in LDS,
 // before the store (the first pass of the direction-by-direction gather-scatter
 // for those faces; the faces between workgroups and the Dirichlet x-faces are
 // left to the gather-scatter).  Each pair is summed as (p-face + 0-face), the
@@ -216,7 +216,7 @@ __device__ __forceinline__ void st(T *p, T v) {
 // GH (FP32 only): the factors come as FP16 pairs from G16, and the element's
 // result is multiplied by gsc[e] before the x-face sums and the store.
 
-template <typename T, bool NT, bool NTS, bool XF, bool GH = false>
+template <typename T, bool NT, bool NTS, int XF, bool GH = false>
 __device__ __forceinline__ void ax8_body(int64_t E, const T *__restrict__ u,
                                          const T *__restrict__ G, const T *__restrict__ Dg,
                                          T *__restrict__ v, int nv, T *sD, T (*sU)[72],
@@ -229,7 +229,8 @@ __device__ __forceinline__ void ax8_body(int64_t E, const T *__restrict__ u,
   if (threadIdx.x < NN) sD[threadIdx.x] = Dg[threadIdx.x];
   __syncthreads();
   int vec;
-  const int64_t e = (int64_t)rhs_block(nv, vec) * 4 + w;
+  constexpr int WV = XF ? XF : 4;  // waves (elements) per workgroup
+  const int64_t e = (int64_t)rhs_block(nv, vec) * WV + w;
   if (e >= E) return;
   u += (int64_t)vec * E * N3;
   v += (int64_t)vec * E * N3;
@@ -303,7 +304,7 @@ __device__ __forceinline__ void ax8_body(int64_t E, const T *__restrict__ u,
     for (int sh = 32; sh > 0; sh >>= 1) d += __shfl_xor(d, sh, 64);
     if (lane == 0) dotp[e] = d;
   }
-  if constexpr (XF) {  // every wave of the block is live (E is a multiple of 4)
+  if constexpr (XF > 0) {  // every wave of the block is live (E is a multiple of XF)
     if (i == 0) {
 #pragma unroll
       for (int k = 0; k < N; ++k) sr[k * N + j] = acc[k];
@@ -313,7 +314,7 @@ __device__ __forceinline__ void ax8_body(int64_t E, const T *__restrict__ u,
       for (int k = 0; k < N; ++k) ss[k * N + j] = acc[k];
     }
     __syncthreads();
-    if (i == N - 1 && w < 3) {
+    if (i == N - 1 && w < WV - 1) {
 #pragma unroll
       for (int k = 0; k < N; ++k) acc[k] = sS[w][k * N + j] + sR[w + 1][k * N + j];
     }
@@ -328,30 +329,30 @@ __device__ __forceinline__ void ax8_body(int64_t E, const T *__restrict__ u,
 }
 
 // register budgets: FP64 at 4 waves/SIMD, FP32 at 6
-template <bool NT, bool NTS, bool XF>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_ax8_f64(
+template <bool NT, bool NTS, int XF>
+__global__ __launch_bounds__((XF == 8 ? 512 : 256)) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_ax8_f64(
     int64_t E, const double *__restrict__ u, const double *__restrict__ G,
     const double *__restrict__ Dg, double *__restrict__ v, int nv, double *dotp) {
-  __shared__ double sD[64], sU[4][72], sR[4][72], sS[4][72];
+  __shared__ double sD[64], sU[XF == 8 ? 8 : 4][72], sR[XF == 8 ? 8 : 4][72], sS[XF == 8 ? 8 : 4][72];
   ax8_body<double, NT, NTS, XF>(E, u, G, Dg, v, nv, sD, sU, sR, sS, dotp);
 }
-template <bool NT, bool NTS, bool XF>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) void k_ax8_f32(
+template <bool NT, bool NTS, int XF>
+__global__ __launch_bounds__((XF == 8 ? 512 : 256)) __attribute__((amdgpu_waves_per_eu(6, 8))) void k_ax8_f32(
     int64_t E, const float *__restrict__ u, const float *__restrict__ G,
     const float *__restrict__ Dg, float *__restrict__ v, int nv) {
-  __shared__ float sD[64], sU[4][72], sR[4][72], sS[4][72];
+  __shared__ float sD[64], sU[XF == 8 ? 8 : 4][72], sR[XF == 8 ? 8 : 4][72], sS[XF == 8 ? 8 : 4][72];
   ax8_body<float, NT, NTS, XF>(E, u, G, Dg, v, nv, sD, sU, sR, sS);
 }
 
-template <bool NT, bool NTS, bool XF>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6, 8))) void k_ax8_f32h(
+template <bool NT, bool NTS, int XF>
+__global__ __launch_bounds__((XF == 8 ? 512 : 256)) __attribute__((amdgpu_waves_per_eu(6, 8))) void k_ax8_f32h(
     int64_t E, const float *__restrict__ u, const uint32_t *__restrict__ G16,
     const float *__restrict__ gsc, const float *__restrict__ Dg, float *__restrict__ v, int nv) {
-  __shared__ float sD[64], sU[4][72], sR[4][72], sS[4][72];
+  __shared__ float sD[64], sU[XF == 8 ? 8 : 4][72], sR[XF == 8 ? 8 : 4][72], sS[XF == 8 ? 8 : 4][72];
   ax8_body<float, NT, NTS, XF, true>(E, u, nullptr, Dg, v, nv, sD, sU, sR, sS, nullptr, G16, gsc);
 }
 
-template <typename T, bool XF>
+template <typename T, int XF>
 static void ax8_launch(const Level &L, const T *u, T *v, const T *G, const T *D, int nv,
                        hipStream_t s, double *dotp) {
   // Several right sides share G through L2: plain loads (non-temporal ones would
@@ -366,15 +367,16 @@ static void ax8_launch(const Level &L, const T *u, T *v, const T *G, const T *D,
   // cache up to 100 MB (32^3, 67 MB in FP32: product 128 us against 133); at 134 MB
   // (32^3 in FP64) they displace what the next call reads (255 us against 236).
   constexpr double kLoadMB = 192.0, kStoreMB = 100.0;
-  const dim3 grid((unsigned)((L.E + 3) / 4 * nv));
+  constexpr int WV = XF ? XF : 4;
+  const dim3 grid((unsigned)((L.E + WV - 1) / WV * nv)), block(64 * WV);
   const double mb = (double)L.nloc * sizeof(T) * 1e-6;
   const bool stream = L.ax_variant == 2 && nv == 1;
   const bool nt = stream && mb * (sizeof(T) == 4 && L.G16 ? 5 : 8) > kLoadMB;
   const bool nts = stream && mb > kStoreMB;
 #define SEM_AX8(K, ...)                                                                       \
-  if (nt && nts) hipLaunchKernelGGL((K<true, true, XF>), grid, dim3(256), 0, s, __VA_ARGS__); \
-  else if (nt) hipLaunchKernelGGL((K<true, false, XF>), grid, dim3(256), 0, s, __VA_ARGS__);  \
-  else hipLaunchKernelGGL((K<false, false, XF>), grid, dim3(256), 0, s, __VA_ARGS__)
+  if (nt && nts) hipLaunchKernelGGL((K<true, true, XF>), grid, block, 0, s, __VA_ARGS__); \
+  else if (nt) hipLaunchKernelGGL((K<true, false, XF>), grid, block, 0, s, __VA_ARGS__);  \
+  else hipLaunchKernelGGL((K<false, false, XF>), grid, block, 0, s, __VA_ARGS__)
   if constexpr (sizeof(T) == 8) {
     SEM_AX8(k_ax8_f64, L.E, u, G, D, v, nv, dotp);
   } else if (L.G16) {  // FP16 factors
@@ -391,10 +393,12 @@ static void ax_n(const Level &L, const T *u, T *v, const T *G, const T *D, int n
                  hipStream_t s, double *dotp) {
   if constexpr (N == 8) {
     if (L.ax_variant >= 1) {
-      if (xf)
-        ax8_launch<T, true>(L, u, v, G, D, nv, s, dotp);
+      if (xf && L.xgroup == 8)
+        ax8_launch<T, 8>(L, u, v, G, D, nv, s, dotp);
+      else if (xf)
+        ax8_launch<T, 4>(L, u, v, G, D, nv, s, dotp);
       else
-        ax8_launch<T, false>(L, u, v, G, D, nv, s, dotp);
+        ax8_launch<T, 0>(L, u, v, G, D, nv, s, dotp);
       return;
     }
   }
@@ -415,7 +419,7 @@ static void ax_n(const Level &L, const T *u, T *v, const T *G, const T *D, int n
 }
 
 bool ax_sums_x_faces(const Level &L, size_t word, int nv) {
-  return L.gs_struct && L.xfuse && L.N == 8 && L.ax_variant >= 1 && L.nex % 4 == 0 &&
+  return L.gs_struct && L.xfuse && L.N == 8 && L.ax_variant >= 1 && L.nex % L.xgroup == 0 &&
          !gs_in_one_launch(L, word, nv);
 }
 

@@ -160,7 +160,7 @@ struct Mf {
   static constexpr int NLX = NK * NK, SX = (NLX + 63) / 64;  // backward x lines (kept rows)
   // floats per wavefront (the last exchange spaces its planes by NK + 1 lines)
   static constexpr int NLB = NK * (NK + 1) > NL ? NK * (NK + 1) : NL, BUF = NLB * LS;
-  static constexpr int WAVES = 4;
+  static constexpr int WAVES = 4;  // without x-face sums
   // 16-bit operands: k in groups of four (forward: the line's nodes; backward:
   // the modes), one register pair of A operands per direction and pass kind
   static constexpr int K4 = (PB + 3) / 4;
@@ -500,8 +500,8 @@ __device__ __attribute__((always_inline)) inline void mf_load(
 }
 
 // the local solve of element e from its loaded inputs; buf = the wave's LDS.
-// XF: the workgroup's four waves hold four consecutive elements along x, and
-// the copies on the three x-faces between them are summed (through xfx, LDS
+// XF > 0: the workgroup's XF (4 or 8) waves hold consecutive elements along x, and
+// the copies on the x-faces between them are summed (through xfx, LDS
 // shared by the workgroup) before the store, each pair as (p-face + 0-face),
 // the order of the gather-scatter's x step, which then covers only the faces
 // between workgroups.
@@ -585,7 +585,7 @@ __device__ __attribute__((always_inline)) inline void mf_load_late(
 // then takes both powers of two back); BF16 keeps FP32's exponent range and
 // needs neither.
 // AS: z receives the whole box, [E][PB^3].
-template <int P, bool RS, int XS, bool YS, bool XF, int OP = kOpF32, bool AS = false>
+template <int P, bool RS, int XS, bool YS, int XF, int OP = kOpF32, bool AS = false>
 __device__ __attribute__((always_inline)) inline void mf_solve(
     const MfIn<P, RS, XS, YS, AS> &in, int64_t e, const float *__restrict__ lamg, float *__restrict__ z,
     float *buf, int lane, float *xfx, int wave, const float *__restrict__ Sg,
@@ -811,7 +811,7 @@ __device__ __attribute__((always_inline)) inline void mf_solve(
       }
     }
   }
-  if constexpr (XF) {
+  if constexpr (XF > 0) {
     constexpr int NLX = F::NLX, GL = (N - 1) / 4, IL = (N - 1) % 4;
 #pragma unroll
     for (int s = 0; s < F::SX; ++s) {
@@ -827,7 +827,7 @@ __device__ __attribute__((always_inline)) inline void mf_solve(
       const int l = 64 * s + lane;
       if (l < NLX) {
         if (wave > 0) o[s][0][0] = xfx[(2 * wave - 1) * NLX + l] + o[s][0][0];
-        if (wave < F::WAVES - 1) o[s][GL][IL] = o[s][GL][IL] + xfx[(2 * wave + 2) * NLX + l];
+        if (wave < XF - 1) o[s][GL][IL] = o[s][GL][IL] + xfx[(2 * wave + 2) * NLX + l];
       }
     }
   }
@@ -857,8 +857,8 @@ __device__ __attribute__((always_inline)) inline void mf_solve(
 // solves C consecutive elements, loading the next element's inputs before it
 // solves the current one, so that the loads of one overlap the other's work.
 // AS: additive Schwarz, z = the boxes.
-template <int P, int C, bool RS, int XS, bool YS, bool XF, bool AS = false>
-__global__ __launch_bounds__(256) void k_fdm_mf32(int64_t E, int nex, int ney, int nez,
+template <int P, int C, bool RS, int XS, bool YS, int XF, bool AS = false>
+__global__ __launch_bounds__((XF == 8 ? 512 : 256)) void k_fdm_mf32(int64_t E, int nex, int ney, int nez,
                                                   const float *__restrict__ r,
                                                   const float *__restrict__ rs,
                                                   const float *__restrict__ Sg,
@@ -868,14 +868,15 @@ __global__ __launch_bounds__(256) void k_fdm_mf32(int64_t E, int nex, int ney, i
   using F = Mf<P, AS>;
   constexpr int N3 = F::N3;
   static_assert(!XF || C == 1, "x-face sums: one element per wave");
-  __shared__ mf4_t lds4[F::WAVES * F::BUF / 4];
-  __shared__ float xfx[XF ? 2 * F::WAVES * F::NLX : 1];
+  constexpr int WV = XF ? XF : F::WAVES;
+  __shared__ mf4_t lds4[WV * F::BUF / 4];
+  __shared__ float xfx[XF ? 2 * WV * F::NLX : 1];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   int vec;
-  const int64_t e0 = ((int64_t)split_rhs(xcd_block(), nv, vec) * F::WAVES + wave) * C;
+  const int64_t e0 = ((int64_t)split_rhs(xcd_block(), nv, vec) * WV + wave) * C;
   // whole wave leaves; only XF waits on other waves, and then E is a multiple
-  // of 4 (every wave of a workgroup is live)
+  // of XF (every wave of a workgroup is live)
   if (e0 >= E) return;
   r += (int64_t)vec * E * N3;
   if (RS) rs += (int64_t)vec * E * N3;
@@ -905,8 +906,8 @@ __global__ __launch_bounds__(256) void k_fdm_mf32(int64_t E, int nex, int ney, i
 // S16 = S_d / s_d as 16-bit patterns, ssc = s_d per element and direction.
 // (at most 6 wavefronts per SIMD asked of the register allocator: aiming
 // higher made it spill some BF16 forms at p = 7)
-template <int P, bool RS, int XS, bool YS, bool XF, int OP>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 6))) void k_fdm_mf16(
+template <int P, bool RS, int XS, bool YS, int XF, int OP>
+__global__ __launch_bounds__((XF == 8 ? 512 : 256)) __attribute__((amdgpu_waves_per_eu(1, 6))) void k_fdm_mf16(
     int64_t E, int nex, int ney, int nez,
                                                   const float *__restrict__ r,
                                                   const float *__restrict__ rs,
@@ -917,13 +918,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 6))) voi
                                                   float *__restrict__ z, int nv) {
   using F = Mf<P>;
   constexpr int N3 = F::N3;
-  __shared__ mf4_t lds4[F::WAVES * F::BUF / 4];
-  __shared__ float xfx[XF ? 2 * F::WAVES * F::NLX : 1];
+  constexpr int WV = XF ? XF : F::WAVES;
+  __shared__ mf4_t lds4[WV * F::BUF / 4];
+  __shared__ float xfx[XF ? 2 * WV * F::NLX : 1];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   int vec;
-  const int64_t e = (int64_t)split_rhs(xcd_block(), nv, vec) * F::WAVES + wave;
-  if (e >= E) return;  // whole wave; XF launches only whole workgroups (E % 4 == 0)
+  const int64_t e = (int64_t)split_rhs(xcd_block(), nv, vec) * WV + wave;
+  if (e >= E) return;  // whole wave; XF launches only whole workgroups (E % XF == 0)
   r += (int64_t)vec * E * N3;
   if (RS) rs += (int64_t)vec * E * N3;
   z += (int64_t)vec * E * N3;
@@ -943,32 +945,31 @@ static RasW ras_w(const Level &L) {
   return w;
 }
 
-template <int P, bool RS, int XS, bool YS, bool XF, int OP = kOpF32>
+template <int P, bool RS, int XS, bool YS, int XF, int OP = kOpF32>
 void mf32_launch_x(const Ctx &c, const Level &L, const float *r, const float *rs, float *z,
                    hipStream_t s, int nv) {
   using F = Mf<P>;
+  constexpr int WV = XF ? XF : F::WAVES;
+  if (XF && (L.E % WV != 0 || c.nex % WV != 0))
+    fail(SEM_EINVAL, "FDM: x-face sums need whole groups of elements along x");
   if constexpr (OP != kOpF32) {
-    if (XF && (L.E % F::WAVES != 0 || c.nex % F::WAVES != 0))
-      fail(SEM_EINVAL, "FDM: x-face sums need whole groups of four elements along x");
     if (!L.A16 || !L.sscale) fail(SEM_EINVAL, "16-bit FDM data were not built");
-    const dim3 grid((unsigned)((L.E + F::WAVES - 1) / F::WAVES * nv));
-    hipLaunchKernelGGL((k_fdm_mf16<P, RS, XS, YS, XF, OP>), grid, dim3(64 * F::WAVES), 0, s, L.E,
+    const dim3 grid((unsigned)((L.E + WV - 1) / WV * nv));
+    hipLaunchKernelGGL((k_fdm_mf16<P, RS, XS, YS, XF, OP>), grid, dim3(64 * WV), 0, s, L.E,
                        c.nex, c.ney, c.nez, r, rs, L.A16, L.sscale, L.lam32, ras_w(L), z, nv);
     SEM_LAUNCH("k_fdm_mf16");
   } else {
     const int C = XF ? 1 : c.fdm_mf32_chain;
-    if (XF && (L.E % F::WAVES != 0 || c.nex % F::WAVES != 0))
-      fail(SEM_EINVAL, "FDM: x-face sums need whole groups of four elements along x");
-    const dim3 grid((unsigned)((L.E + F::WAVES * C - 1) / (F::WAVES * C) * nv));
-    const dim3 block(64 * F::WAVES);
-    if constexpr (XF) {
-      hipLaunchKernelGGL((k_fdm_mf32<P, 1, RS, XS, YS, true>), grid, block, 0, s, L.E, c.nex,
+    const dim3 grid((unsigned)((L.E + WV * C - 1) / (WV * C) * nv));
+    const dim3 block(64 * WV);
+    if constexpr (XF > 0) {
+      hipLaunchKernelGGL((k_fdm_mf32<P, 1, RS, XS, YS, XF>), grid, block, 0, s, L.E, c.nex,
                          c.ney, c.nez, r, rs, L.S32, L.lam32, ras_w(L), z, nv);
     } else if (C == 2) {
-      hipLaunchKernelGGL((k_fdm_mf32<P, 2, RS, XS, YS, false>), grid, block, 0, s, L.E, c.nex,
+      hipLaunchKernelGGL((k_fdm_mf32<P, 2, RS, XS, YS, 0>), grid, block, 0, s, L.E, c.nex,
                          c.ney, c.nez, r, rs, L.S32, L.lam32, ras_w(L), z, nv);
     } else {
-      hipLaunchKernelGGL((k_fdm_mf32<P, 1, RS, XS, YS, false>), grid, block, 0, s, L.E, c.nex,
+      hipLaunchKernelGGL((k_fdm_mf32<P, 1, RS, XS, YS, 0>), grid, block, 0, s, L.E, c.nex,
                          c.ney, c.nez, r, rs, L.S32, L.lam32, ras_w(L), z, nv);
     }
     SEM_LAUNCH("k_fdm_mf32");
@@ -987,7 +988,7 @@ void mf32_launch_asm(const Ctx &c, const Level &L, const float *r, const float *
     fail(SEM_EINVAL, "FDM: unknown form of the deferred gather-scatter steps");
   const dim3 grid((unsigned)((L.E + F::WAVES - 1) / F::WAVES)), block(64 * F::WAVES);
 #define SEM_ASM_LAUNCH(RS, XS, YS)                                                               \
-  hipLaunchKernelGGL((k_fdm_mf32<P, 1, RS, XS, YS, false, true>), grid, block, 0, s, L.E, c.nex, \
+  hipLaunchKernelGGL((k_fdm_mf32<P, 1, RS, XS, YS, 0, true>), grid, block, 0, s, L.E, c.nex, \
                      c.ney, c.nez, r, rs, L.S32, L.lam32, ras_w(L), z, 1)
   if (rs) {
     if (which == 2 && ys) SEM_ASM_LAUNCH(true, 2, true);
@@ -1016,23 +1017,26 @@ void mf32_launch(const Ctx &c, const Level &L, const float *r, const float *rs, 
   if (xin & ~15 || which == 3 || (ys && which == 0) || (xf && which == 1))
     fail(SEM_EINVAL, "FDM: unknown form of the deferred gather-scatter steps");
   if (which == 2 && !rs) fail(SEM_EINVAL, "FDM: no subtrahend to take the x step");
+  const bool x8 = xf && L.xgroup == 8;
+#define SEM_MF_LAUNCH(RS, XS, YS, XF) mf32_launch_x<P, RS, XS, YS, XF, OP>(c, L, r, rs, z, s, nv)
+#define SEM_MF_XF(RS, XS, YS)                     \
+  do {                                            \
+    if (x8) SEM_MF_LAUNCH(RS, XS, YS, 8);         \
+    else if (xf) SEM_MF_LAUNCH(RS, XS, YS, 4);    \
+    else SEM_MF_LAUNCH(RS, XS, YS, 0);            \
+  } while (0)
   if (rs) {
     if (which == 1) fail(SEM_EINVAL, "FDM: the x step is taken on the subtrahend only");
-    if (xf) {
-      if (which == 2 && ys) mf32_launch_x<P, true, 2, true, true, OP>(c, L, r, rs, z, s, nv);
-      else if (which == 2) mf32_launch_x<P, true, 2, false, true, OP>(c, L, r, rs, z, s, nv);
-      else mf32_launch_x<P, true, 0, false, true, OP>(c, L, r, rs, z, s, nv);
-    } else {
-      if (which == 2 && ys) mf32_launch_x<P, true, 2, true, false, OP>(c, L, r, rs, z, s, nv);
-      else if (which == 2) mf32_launch_x<P, true, 2, false, false, OP>(c, L, r, rs, z, s, nv);
-      else mf32_launch_x<P, true, 0, false, false, OP>(c, L, r, rs, z, s, nv);
-    }
+    if (which == 2 && ys) SEM_MF_XF(true, 2, true);
+    else if (which == 2) SEM_MF_XF(true, 2, false);
+    else SEM_MF_XF(true, 0, false);
   } else {
-    if (xf) mf32_launch_x<P, false, 0, false, true, OP>(c, L, r, rs, z, s, nv);
-    else if (which == 1 && ys) mf32_launch_x<P, false, 1, true, false, OP>(c, L, r, rs, z, s, nv);
-    else if (which == 1) mf32_launch_x<P, false, 1, false, false, OP>(c, L, r, rs, z, s, nv);
-    else mf32_launch_x<P, false, 0, false, false, OP>(c, L, r, rs, z, s, nv);
+    if (which == 1 && ys) SEM_MF_LAUNCH(false, 1, true, 0);
+    else if (which == 1) SEM_MF_LAUNCH(false, 1, false, 0);
+    else SEM_MF_XF(false, 0, false);
   }
+#undef SEM_MF_XF
+#undef SEM_MF_LAUNCH
 }
 
 // Setup of L.A16 from the 16-bit factors S16 = S_d / s_d ([E][3][pb][pb]):

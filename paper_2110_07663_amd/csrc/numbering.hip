@@ -332,29 +332,29 @@ __global__ void k_gs_dir(T *__restrict__ v, GsGrid g, int64_t E) {
   if (pos == cnt - 1 && bhi) v[hi] = T(0);
 }
 
-// The x pass when the faces inside each group of 4 consecutive elements along x
+// The x pass when the faces inside each group of W consecutive elements along x
 // are summed already: thread (group q, line) sums the face between the group's
 // last element and the next group's first, and zeroes the Dirichlet x-faces of
 // the row ends (the low face of the group's first element, the high face of
-// its last).  Requires nex to be a multiple of 4.
+// its last).  Requires nex to be a multiple of W.
 template <typename T>
-__global__ void k_gs_xb(T *__restrict__ v, GsGrid g, int64_t E) {
+__global__ void k_gs_xb(T *__restrict__ v, GsGrid g, int64_t E, int W) {
   const int64_t t = xcd_block() * (int64_t)blockDim.x + threadIdx.x;
   const int N = g.N, N2 = N * N;
-  const int64_t groups = E / 4;
+  const int64_t groups = E / W;
   if (t >= groups * N2) return;
   v += blockIdx.y * E * N2 * N;  // right side blockIdx.y
   const unsigned ut = (unsigned)t;
   const int64_t q = ut / (unsigned)N2;
   const int rem = (int)(ut - (unsigned)q * (unsigned)N2);
   const int64_t N3 = (int64_t)N2 * N;
-  const int64_t e0 = 4 * q, e3 = e0 + 3;
-  const int64_t ex0 = e0 % g.nex, ex3 = ex0 + 3;
+  const int64_t e0 = W * q, e1 = e0 + W - 1;
+  const int64_t ex0 = (unsigned)e0 % (unsigned)g.nex, ex1 = ex0 + W - 1;
   const int64_t line = (int64_t)rem * N;
   if (g.bc[0] && ex0 == 0) v[e0 * N3 + line] = T(0);
-  const int64_t hi = e3 * N3 + line + g.p;
-  if (ex3 + 1 < g.nex) {
-    const int64_t lo = (e3 + 1) * N3 + line;
+  const int64_t hi = e1 * N3 + line + g.p;
+  if (ex1 + 1 < g.nex) {
+    const int64_t lo = (e1 + 1) * N3 + line;
     const T sum = v[hi] + v[lo];
     v[hi] = sum;
     v[lo] = sum;
@@ -563,8 +563,8 @@ bool gs_in_one_launch(const Level &L, size_t word, int nv) {
 template <typename T>
 void launch_gs(const Level &L, T *v, hipStream_t s, int nv, bool x_in_blocks, bool skip_x,
                bool skip_y) {
-  if (x_in_blocks && (!L.gs_struct || L.nex % 4 != 0))
-    fail(SEM_EINVAL, "gather-scatter: block x-faces need the direction passes and nex % 4 == 0");
+  if (x_in_blocks && (!L.gs_struct || L.nex % L.xgroup != 0))
+    fail(SEM_EINVAL, "gather-scatter: block x-faces need the direction passes and whole groups along x");
   if ((skip_x || skip_y) && !L.gs_struct)
     fail(SEM_EINVAL, "gather-scatter: skipping a pass needs the direction passes");
   if (L.gs_struct) {
@@ -587,8 +587,8 @@ void launch_gs(const Level &L, T *v, hipStream_t s, int nv, bool x_in_blocks, bo
     if (skip_x) {
       // the consumer takes the x step (the passes commute up to rounding)
     } else if (x_in_blocks) {
-      const dim3 gx(nb(L.E / 4 * L.N * L.N, 256), (unsigned)nv);
-      hipLaunchKernelGGL((k_gs_xb<T>), gx, dim3(256), 0, s, v, g, L.E);
+      const dim3 gx(nb(L.E / L.xgroup * L.N * L.N, 256), (unsigned)nv);
+      hipLaunchKernelGGL((k_gs_xb<T>), gx, dim3(256), 0, s, v, g, L.E, L.xgroup);
       SEM_LAUNCH("k_gs_xb");
     } else {
       hipLaunchKernelGGL((k_gs_dir<T, 0>), dim3(grid), dim3(256), 0, s, v, g, L.E);

@@ -108,6 +108,7 @@ struct Level {
   int bc[6] = {0, 0, 0, 0, 0, 0};
   bool gs_struct = true;             // false: the sorted-numbering segments (perm/off)
   bool xfuse = true;                 // the p = 7 Ax sums x-faces inside its workgroups
+  int xgroup = 4;                    // elements along x per workgroup that sums its x-faces
   int gs_yz = -1;                    // y and z passes in one launch: 1 yes, 0 no, -1 FP64 only
   int gs_all = -1;                   // all passes in one launch: 1 yes, 0 no, -1 small levels only
   bool xdefer = true;                // Chebyshev updates may take the x step of S's gather-scatter
@@ -306,7 +307,7 @@ template <typename T>
 void launch_gather(const Ctx &c, const Level &L, const double *ug, T *ul, hipStream_t s,
                    int nv = 1, int64_t ug_stride = 0);
 // nv > 1: nv vectors nloc apart (several right sides of one problem)
-// x_in_blocks: the x-faces inside each group of 4 elements along x are summed
+// x_in_blocks: the x-faces inside each group of L.xgroup elements along x are summed
 // already (Ax with xf); only the faces between groups and the Dirichlet x-faces
 // remain for the x pass
 template <typename T>

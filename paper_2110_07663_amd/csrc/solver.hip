@@ -330,6 +330,13 @@ static void init_ctx(Ctx &c, const sem_mesh *m, int p, const int8_t *bc, const s
       // SEM_AX_XFUSE=0: the p = 7 Ax leaves every x-face to the gather-scatter
       const char *xfv = getenv("SEM_AX_XFUSE");
       L.xfuse = !(xfv && xfv[0] == '0');
+      // Elements along x in a workgroup that sums the x-faces it shares (Ax at p = 7,
+      // FDM): 8 where they divide the line, else 4; SEM_XGROUP=4 keeps 4.  The
+      // gather-scatter's x pass, which touches a cache line per face node, is left
+      // with the faces between groups: at 32^3 (p = 7) 14.5 us with groups of 8, 28 with
+      // 4 in FP64 (the product 224 and 236), 7.3 and 12.4 in FP32 (Schwarz 99.7, 102.6).
+      const char *xgv = getenv("SEM_XGROUP");
+      L.xgroup = m->nex % 8 == 0 && !(xgv && xgv[0] == '4') ? 8 : 4;
       // SEM_GS_XDEFER=0: the gather-scatter after an FDM that only feeds a
       // Chebyshev update takes its x step itself
       const char *xdv = getenv("SEM_GS_XDEFER");
@@ -556,12 +563,11 @@ static bool fdm_takes_y_step(const Ctx &c, const Level &L) {
 }
 
 // Whether the FP32 matrix-core RAS kernel sums the x-faces its workgroup
-// shares (four consecutive elements along x) before it stores
+// shares (L.xgroup consecutive elements along x) before it stores
 template <typename T>
 static bool fdm_sums_x_faces(const Ctx &c, const Level &L, int nv) {
   return sizeof(T) == 4 && c.fdm_xfaces && c.opts.smoother == SEM_SMOOTH_RAS && fdm_in_mf(c, L) &&
-         L.gs_struct && !gs_in_one_launch(L, sizeof(T), nv) && L.nex % 4 == 0 &&
-         L.E % 4 == 0;
+         L.gs_struct && !gs_in_one_launch(L, sizeof(T), nv) && L.nex % L.xgroup == 0;
 }
 
 // A u with the x step (and, when the smoother takes it, the y step) of the
