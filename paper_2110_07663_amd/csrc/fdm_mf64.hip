@@ -31,7 +31,7 @@ namespace sem {
 
 namespace {
 
-template <int P, bool ASM>
+template <int P, bool ASM, int WPE = 1>  // WPE: wavefronts per element
 struct Md {
   static constexpr int PB = P + 3, N = P + 1, N3 = N * N * N;
   static constexpr int K4 = (PB + 3) / 4;        // groups of four k or modes
@@ -53,12 +53,14 @@ struct Md {
   static constexpr int Y = PB | 1, X = PB * Y;
   // Lanes past the last line read (and never write): their second digit is
   // held at the last one, and BOX covers every address they then form.
-  static constexpr int D3 = 16 * S3 - 1 - (PB - 1) * PB, D1 = 16 * S1 - 1 - (NK - 1) * NK;
-  static constexpr int R1 = 16 * S3 - 1 + (PB - 1) * (X + Y - PB), R2 = D3 + (PB - 1) * (X + Y);
+  // (slots in multiples of the element's waves)
+  static constexpr int Q3 = (S3 + WPE - 1) / WPE * WPE * 16, Q1 = (S1 + WPE - 1) / WPE * WPE * 16;
+  static constexpr int D3 = Q3 - 1 - (PB - 1) * PB, D1 = Q1 - 1 - (NK - 1) * NK;
+  static constexpr int R1 = Q3 - 1 + (PB - 1) * (X + Y - PB), R2 = D3 + (PB - 1) * (X + Y);
   static constexpr int R3 = D1 * Y + (NK - 1) * X + PB - 1, R12 = R1 > R2 ? R1 : R2;
   static constexpr int BOX = (R12 > R3 ? R12 : R3) + 1;
-  static constexpr int BUF = BOX + 3 * PB + 16;  // + the eigenvalues
-  static_assert(D3 < PB + 16, "eigenvalue reads of the padding lanes leave the buffer");
+  static constexpr int LAM = D3 < PB ? 3 * PB : 2 * PB + D3 + 1;  // eigenvalues, and what those lanes read
+  static constexpr int BUF = BOX + LAM;
   static constexpr int WAVES = 4;
 };
 
@@ -88,10 +90,15 @@ __device__ inline double md_inv(double d) {
   return __builtin_fma(y, __builtin_fma(-d, y, 1.0), y);
 }
 
-// orders the LDS traffic of one wavefront between passes
+// orders the LDS traffic of the element's wavefronts between passes
+template <int WPE>
 __device__ inline void md_sync() {
-  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0) only
-  __builtin_amdgcn_wave_barrier();
+  if constexpr (WPE > 1) {
+    __syncthreads();
+  } else {
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0) only
+    __builtin_amdgcn_wave_barrier();
+  }
 }
 
 // A operands of direction d: forward (k group, m group) -> lane (k, m) holds
@@ -156,25 +163,32 @@ struct RasGrid {
 // formed from the grid position: exact, equal to the assembled weight);
 // ASM: z = the whole boxes [E][PB^3].
 // RS: the local solves act on r - rs (a residual formed as it is read).
-template <int P, bool ASM, bool RS>
+// WPE: wavefronts per element.  One (four elements per workgroup) fills the device
+// from a few thousand elements on; below, a launch lasts as long as one element's
+// chain of passes, and WPE = 4 (one element per workgroup, its line slots dealt
+// out to the waves, workgroup barriers between the passes) shortens that.
+template <int P, bool ASM, bool RS, int WPE>
 __global__ __launch_bounds__(256) void k_fdm_mf64(int64_t E, int nex, int ney, int nez,
                                                   const double *__restrict__ r,
                                                   const double *__restrict__ rs,
                                                   const double *__restrict__ Sg,
                                                   const double *__restrict__ lamg, RasGrid W,
                                                   double *__restrict__ z, int nv) {
-  using F = Md<P, ASM>;
+  using F = Md<P, ASM, WPE>;
   constexpr int PB = F::PB, N = F::N, N3 = F::N3, K4 = F::K4, KG = F::KG, NK = F::NK;
-  __shared__ double lds[F::WAVES * F::BUF];
+  constexpr int EPB = F::WAVES / WPE;
+  __shared__ double lds[EPB * F::BUF];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int sub = wave % WPE;  // the wave takes the slots sub, sub + WPE, ...
+  constexpr int S3 = (F::S3 + WPE - 1) / WPE, S2 = (F::S2 + WPE - 1) / WPE, S1 = (F::S1 + WPE - 1) / WPE;
   const int lane = threadIdx.x & 63, hi = lane >> 4, lo = lane & 15;
   int vec;
-  const int64_t e = (int64_t)split_rhs(xcd_block(), nv, vec) * F::WAVES + wave;
-  if (e >= E) return;  // whole wave; no workgroup barriers below
+  const int64_t e = (int64_t)split_rhs(xcd_block(), nv, vec) * EPB + wave / WPE;
+  if (e >= E) return;  // whole wave (WPE = 1: no workgroup barriers below), else whole workgroup
   r += (int64_t)vec * E * N3;
   if (RS) rs += (int64_t)vec * E * N3;
   z += (int64_t)vec * E * (ASM ? PB * PB * PB : N3);
-  double *buf = lds + wave * F::BUF, *lam = buf + F::BOX;
+  double *buf = lds + wave / WPE * F::BUF, *lam = buf + F::BOX;
   // the wave's reads start at most a plane, a line and an element below e
   const int64_t back = (int64_t)nex * ney + nex + 1, eb = e > back ? e - back : 0;
   const int64_t wb = (E - eb) * N3 * 8;
@@ -184,17 +198,20 @@ __global__ __launch_bounds__(256) void k_fdm_mf64(int64_t E, int nex, int ney, i
 
   double Af[K4 * K4], Ab[K4 * KG];
   md_forward_op<P, ASM>(Se, 2, lane, Af);
-  if (lane < 3 * PB) lam[lane] = fmin(lamg[e * 3 * PB + lane], kHuge);
+  if (sub == 0 && lane < 3 * PB) lam[lane] = fmin(lamg[e * 3 * PB + lane], kHuge);
 
   int64_t ex64, ey64, ez64;
   elem_coords(e, nex, ney, ex64, ey64, ez64);
   const int ex = (int)ex64, ey = (int)ey64, ez = (int)ez64;
+  // first line of the wave's slot s, and a bound on its last over the waves
+  auto at0 = [&](int s) { return 16 * (WPE * s + sub); };
+  auto last = [](int s) constexpr { return 16 * (WPE * s + WPE - 1) + 15; };
   // the second digits of the lane's lines
-  int hi3[F::S3];
+  int hi3[S3];
 #pragma unroll
-  for (int s = 0; s < F::S3; ++s) {
-    const int d = (16 * s + lo) / PB;
-    hi3[s] = 16 * s + 15 < F::L3 ? d : (d < PB ? d : PB - 1);
+  for (int s = 0; s < S3; ++s) {
+    const int d = (at0(s) + lo) / PB;
+    hi3[s] = last(s) < F::L3 ? d : (d < PB ? d : PB - 1);
   }
   // z forward on the box lines (a, b): node c = 4kg + hi of the lane's line.
   // Byte offsets from element eb; a neighbour outside the domain sets bit 31,
@@ -219,18 +236,18 @@ __global__ __launch_bounds__(256) void k_fdm_mf64(int64_t E, int nex, int ney, i
   const uint32_t base = (uint32_t)(e - eb) * (N3 * 8);
   const uint32_t xl = ex == 0 ? kO : 0, xr = ex == nex - 1 ? kO : 0;
   const uint32_t yl = ey == 0 ? kO : 0, yr = ey == ney - 1 ? kO : 0;
-  double f3[F::S3][K4];
+  double f3[S3][K4];
   {
-    double in[F::S3][K4];
+    double in[S3][K4];
 #pragma unroll
-    for (int s = 0; s < F::S3; ++s) {
-      const int b = hi3[s], a = 16 * s + lo - b * PB;
+    for (int s = 0; s < S3; ++s) {
+      const int b = hi3[s], a = at0(s) + lo - b * PB;
       uint32_t at = (uint32_t)((b - 1) * N + a - 1) * 8, bit = 0;
       at = a == 0 ? at + (P - N3) * 8 : (a == PB - 1 ? at + (N3 - P) * 8 : at);
       bit = a == 0 ? xl : (a == PB - 1 ? xr : 0);
       at = b == 0 ? at + P * N * 8 - line : (b == PB - 1 ? at - P * N * 8 + line : at);
       bit |= b == 0 ? yl : (b == PB - 1 ? yr : 0);
-      if (16 * s + 15 >= F::L3) bit = 16 * s + lo >= F::L3 ? kO : bit;
+      if (last(s) >= F::L3) bit = at0(s) + lo >= F::L3 ? kO : bit;
       at += base;
 #pragma unroll
       for (int kg = 0; kg < K4; ++kg) {
@@ -239,92 +256,92 @@ __global__ __launch_bounds__(256) void k_fdm_mf64(int64_t E, int nex, int ney, i
         if constexpr (RS) in[s][kg] -= rsb.ld(off);
       }
     }
-    md_contract<F::S3, K4, K4>(Af, [&](int s, int kg) { return in[s][kg]; }, f3);
+    md_contract<S3, K4, K4>(Af, [&](int s, int kg) { return in[s][kg]; }, f3);
   }
   md_forward_op<P, ASM>(Se, 1, lane, Af);
 #pragma unroll
-  for (int s = 0; s < F::S3; ++s) {
-    const int l = 16 * s + lo, b = hi3[s], at = (l - b * PB) * F::Y + b * F::X + hi;
+  for (int s = 0; s < S3; ++s) {
+    const int l = at0(s) + lo, b = hi3[s], at = (l - b * PB) * F::Y + b * F::X + hi;
 #pragma unroll
     for (int g = 0; g < K4; ++g)
       if (l < F::L3 && 4 * g + hi < PB) buf[at + 4 * g] = f3[s][g];
   }
-  md_sync();
+  md_sync<WPE>();
   // the lane's k in each group, 0 past the box (its factor entries are zero)
   int kc[K4];
 #pragma unroll
   for (int kg = 0; kg < K4; ++kg) kc[kg] = 4 * kg + hi < PB ? 4 * kg + hi : 0;
-  int at3[F::S3];  // d0 + Y d1 of the lane's lines
+  int at3[S3];  // d0 + Y d1 of the lane's lines
 #pragma unroll
-  for (int s = 0; s < F::S3; ++s) at3[s] = 16 * s + lo + hi3[s] * (F::Y - PB);
+  for (int s = 0; s < S3; ++s) at3[s] = at0(s) + lo + hi3[s] * (F::Y - PB);
   // y forward on the lines (c', a)
-  md_contract<F::S3, K4, K4>(
+  md_contract<S3, K4, K4>(
       Af, [&](int s, int kg) { return buf[at3[s] + kc[kg] * F::X]; }, f3);
   md_forward_op<P, ASM>(Se, 0, lane, Af);
-  md_sync();
+  md_sync<WPE>();
 #pragma unroll
-  for (int s = 0; s < F::S3; ++s)
+  for (int s = 0; s < S3; ++s)
 #pragma unroll
     for (int g = 0; g < K4; ++g)
-      if (16 * s + lo < F::L3 && 4 * g + hi < PB) buf[at3[s] + (4 * g + hi) * F::X] = f3[s][g];
-  md_sync();
+      if (at0(s) + lo < F::L3 && 4 * g + hi < PB) buf[at3[s] + (4 * g + hi) * F::X] = f3[s][g];
+  md_sync<WPE>();
   // x forward on the lines (c', b'), division, x backward in registers
   md_backward_op<P, ASM>(Se, 0, lane, Ab);
-  md_contract<F::S3, K4, K4>(
+  md_contract<S3, K4, K4>(
       Af,
       [&](int s, int kg) {
-        return buf[16 * s + lo - hi3[s] * PB + hi3[s] * F::X + kc[kg] * F::Y];
+        return buf[at0(s) + lo - hi3[s] * PB + hi3[s] * F::X + kc[kg] * F::Y];
       },
       f3);
-  double b3[F::S3][KG], lx[K4];
+  double b3[S3][KG], lx[K4];
 #pragma unroll
   for (int g = 0; g < K4; ++g) lx[g] = lam[kc[g]];
 #pragma unroll
-  for (int s = 0; s < F::S3; ++s) {
-    const double lyz = lam[PB + hi3[s]] + lam[2 * PB + 16 * s + lo - hi3[s] * PB];
+  for (int s = 0; s < S3; ++s) {
+    const double lyz = lam[PB + hi3[s]] + lam[2 * PB + at0(s) + lo - hi3[s] * PB];
 #pragma unroll
     for (int g = 0; g < K4; ++g) f3[s][g] *= md_inv(lyz + lx[g]);
   }
-  md_contract<F::S3, K4, KG>(Ab, [&](int s, int kg) { return f3[s][kg]; }, b3);
+  md_contract<S3, K4, KG>(Ab, [&](int s, int kg) { return f3[s][kg]; }, b3);
   md_backward_op<P, ASM>(Se, 1, lane, Ab);
-  md_sync();
+  md_sync<WPE>();
 #pragma unroll
-  for (int s = 0; s < F::S3; ++s)
+  for (int s = 0; s < S3; ++s)
 #pragma unroll
     for (int g = 0; g < KG; ++g)
-      if (16 * s + lo < F::L3 && 4 * g + hi < NK) buf[at3[s] + (4 * g + hi) * F::X] = b3[s][g];
-  md_sync();
+      if (at0(s) + lo < F::L3 && 4 * g + hi < NK) buf[at3[s] + (4 * g + hi) * F::X] = b3[s][g];
+  md_sync<WPE>();
   // y backward on the lines (c', i)
-  double b2[F::S2][KG];
-  md_contract<F::S2, K4, KG>(
+  double b2[S2][KG];
+  md_contract<S2, K4, KG>(
       Ab,
       [&](int s, int kg) {
-        return buf[16 * s + lo - hi3[s] * PB + hi3[s] * F::X + kc[kg] * F::Y];
+        return buf[at0(s) + lo - hi3[s] * PB + hi3[s] * F::X + kc[kg] * F::Y];
       },
       b2);
   md_backward_op<P, ASM>(Se, 2, lane, Ab);
-  md_sync();
+  md_sync<WPE>();
 #pragma unroll
-  for (int s = 0; s < F::S2; ++s)
+  for (int s = 0; s < S2; ++s)
 #pragma unroll
     for (int g = 0; g < KG; ++g)
-      if (16 * s + lo < F::L2 && 4 * g + hi < NK) buf[at3[s] + (4 * g + hi) * F::X] = b2[s][g];
-  md_sync();
+      if (at0(s) + lo < F::L2 && 4 * g + hi < NK) buf[at3[s] + (4 * g + hi) * F::X] = b2[s][g];
+  md_sync<WPE>();
   // z backward on the lines (i, j): the kept nodes of the element
-  double b1[F::S1][KG];
-  md_contract<F::S1, K4, KG>(
+  double b1[S1][KG];
+  md_contract<S1, K4, KG>(
       Ab,
       [&](int s, int kg) {
-        const int l = 16 * s + lo, d = l / NK;
-        const int j = 16 * s + 15 < F::L1 ? d : (d < NK ? d : NK - 1);
+        const int l = at0(s) + lo, d = l / NK;
+        const int j = last(s) < F::L1 ? d : (d < NK ? d : NK - 1);
         return buf[(l - j * NK) * F::Y + j * F::X + kc[kg]];
       },
       b1);
   if constexpr (ASM) {
     double *zb = z + e * PB * PB * PB;
 #pragma unroll
-    for (int s = 0; s < F::S1; ++s) {
-      const int l = 16 * s + lo;
+    for (int s = 0; s < S1; ++s) {
+      const int l = at0(s) + lo;
 #pragma unroll
       for (int g = 0; g < KG; ++g)
         if (l < F::L1 && 4 * g + hi < PB) zb[(4 * g + hi) * PB * PB + l] = b1[s][g];
@@ -335,8 +352,8 @@ __global__ __launch_bounds__(256) void k_fdm_mf64(int64_t E, int nex, int ney, i
 #pragma unroll
     for (int g = 0; g < KG; ++g) wk[g] = node_w1(4 * g + hi, N, ez, nez, W.bcm, 4);
 #pragma unroll
-    for (int s = 0; s < F::S1; ++s) {
-      const int l = 16 * s + lo, i = l % N, j = l / N;
+    for (int s = 0; s < S1; ++s) {
+      const int l = at0(s) + lo, i = l % N, j = l / N;
       const double wij =
           node_w1(i, N, ex, nex, W.bcm, 0) * node_w1(j, N, ey, ney, W.bcm, 2);
 #pragma unroll
@@ -346,19 +363,31 @@ __global__ __launch_bounds__(256) void k_fdm_mf64(int64_t E, int nex, int ney, i
   }
 }
 
+// Four waves per element up to half a wave per SIMD (1024) and from p = 7, where an
+// element has enough slots of lines to deal out.  With the assembly, one against
+// four: 512 elements p = 7 14.9 / 13.3 us, p = 9 17.3 / 15.4, p = 10 22.6 / 18.7, p =
+// 5 9.8 / 10.4; 768 elements p = 7 16.6 / 16.5; 1728 elements p = 9 32.4 / 34.4.
+constexpr int kWideP = 7;
+constexpr int64_t kWideElements = 640;
+
 template <int P, bool ASM>
 void mf64_launch(const Ctx &c, const Level &L, const double *r, const double *rs, double *z,
                  hipStream_t s, int nv) {
   using F = Md<P, ASM>;
   RasGrid W{0};
   for (int f = 0; f < 6; ++f) W.bcm |= (L.bc[f] ? 1 : 0) << f;
-  const dim3 grid((unsigned)((L.E + F::WAVES - 1) / F::WAVES * nv)), block(64 * F::WAVES);
-  if (rs)
-    hipLaunchKernelGGL((k_fdm_mf64<P, ASM, true>), grid, block, 0, s, L.E, c.nex, c.ney, c.nez, r,
-                       rs, L.S64, L.lam64, W, z, nv);
-  else
-    hipLaunchKernelGGL((k_fdm_mf64<P, ASM, false>), grid, block, 0, s, L.E, c.nex, c.ney, c.nez, r,
-                       r, L.S64, L.lam64, W, z, nv);
+  const bool wide = P >= kWideP && L.E * nv <= kWideElements;
+  const int epb = wide ? F::WAVES / 4 : F::WAVES;
+  const dim3 grid((unsigned)((L.E + epb - 1) / epb * nv)), block(64 * F::WAVES);
+  constexpr int WPE = P >= kWideP ? 4 : 1;
+#define SEM_MF64_LAUNCH(RS, WPE)                                                                   \
+  hipLaunchKernelGGL((k_fdm_mf64<P, ASM, RS, WPE>), grid, block, 0, s, L.E, c.nex, c.ney, c.nez, r, \
+                     RS ? rs : r, L.S64, L.lam64, W, z, nv)
+  if (rs && wide) SEM_MF64_LAUNCH(true, WPE);
+  else if (rs) SEM_MF64_LAUNCH(true, 1);
+  else if (wide) SEM_MF64_LAUNCH(false, WPE);
+  else SEM_MF64_LAUNCH(false, 1);
+#undef SEM_MF64_LAUNCH
   SEM_LAUNCH("k_fdm_mf64");
 }
 

@@ -14,6 +14,8 @@ CASES = [(2, (3, 2, 2), (1,) * 6), (3, (3, 3, 2), (1, 0, 1, 1, 0, 1)), (4, (2, 3
          (5, (3, 2, 3), (1, 1, 0, 1, 1, 0)), (6, (2, 2, 2), (1,) * 6),
          (7, (5, 3, 2), (0, 1, 1, 0, 1, 1)), (7, (1, 1, 1), (1,) * 6), (8, (2, 2, 3), (1,) * 6),
          (9, (3, 2, 2), (0, 0, 1, 1, 0, 1)), (10, (2, 1, 2), (1, 1, 1, 0, 1, 1)),
+         # above 640 elements a wave solves a whole element also from p = 7 on
+         (7, (9, 9, 8), (1, 1, 0, 1, 1, 0)),
          (4, (1, 1, 1), (0,) * 6)]  # a floating box: its constant mode is dropped
 
 
