@@ -253,9 +253,22 @@ __device__ inline VT read_t(const VT *__restrict__ tv, int64_t m, const XDev &f)
   return v;
 }
 
+// Entries per vector of the form that takes the x (and y) step: 16 bytes, or in
+// FP32 8 bytes where only those fit the element rows (N = 6, 10); 0: not possible.
+// n a multiple of the rows, vectors aligned.  (FP32 Cheby-RAS(2) smoothing at p = 9,
+// 16^3: 225 -> 212 us with 8-byte vectors, at p = 5, 24^3: 174 -> 163 us.)
+template <typename T>
+static int xy_width(int N, int64_t n, std::initializer_list<const void *> ps) {
+  constexpr int W = 16 / sizeof(T);
+  if (N % W == 0) return vec16_ok<T>(n, ps) ? W : 0;
+  if (sizeof(T) != 4 || N % 2 != 0 || n % 2 != 0) return 0;
+  for (const void *q : ps)
+    if (q && (reinterpret_cast<uintptr_t>(q) & 7) != 0) return 0;
+  return 2;
+}
 template <typename T>
 bool cheb_can_defer_x(int N, int64_t n, std::initializer_list<const void *> ps) {
-  return N % (int)(16 / sizeof(T)) == 0 && vec16_ok<T>(n, ps);
+  return xy_width<T>(N, n, ps) != 0;
 }
 template bool cheb_can_defer_x<float>(int, int64_t, std::initializer_list<const void *>);
 template bool cheb_can_defer_x<double>(int, int64_t, std::initializer_list<const void *>);
@@ -378,7 +391,16 @@ static void cheb_dispatch(int64_t n, const XDefer &xd, std::initializer_list<con
   if (xd.on && xd.all) {
     with(T{}, integral_constant<int, kAll>{}, std::false_type{}, n, xdev<T>(xd, 1));
   } else if (xd.on) {
-    if (!vec) fail(SEM_EINVAL, "deferred x step needs the vector form");
+    int w = xy_width<T>(xd.N, n, ps);
+    if (xd.dinv && xy_width<T>(xd.N, xd.nloc, {xd.dinv}) != w) w = 0;
+    if (w == 0) fail(SEM_EINVAL, "deferred x step needs the vector form");
+    if constexpr (sizeof(T) == 4) {
+      if (w == 2) {
+        typedef float F2 __attribute__((ext_vector_type(2)));
+        with(F2{}, integral_constant<int, kXY>{}, std::false_type{}, n / 2, xdev<T>(xd, 2));
+        return;
+      }
+    }
     if (cheb_streams<T>(n))
       with(VT{}, integral_constant<int, kXY>{}, std::true_type{}, n / W, xdev<T>(xd));
     else
