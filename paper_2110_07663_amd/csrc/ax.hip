@@ -48,13 +48,18 @@ __device__ __forceinline__ float half_hi(uint32_t w) {
 }
 
 // GH: the factors come from G16 / gsc instead of G (FP32 only)
-template <int N, typename T, bool GH>
+// DOT: element e's share of u^T A_L u goes to dotp[e] (see ax8_body), summed over
+// the element's columns by an LDS tree in a fixed order.  An FCG iteration against a
+// weighted dot over u and v, us: p = 3, 64 elements 93.8 to 90.5, 1000 elements
+// 105.8 to 100.7; p = 5, 512 elements 118.1 to 113.1; p = 9, 216 elements 156.6 to 152.4
+template <int N, typename T, bool GH, bool DOT = false>
 __global__ __launch_bounds__(AxShape<N>::BS) void k_ax(int64_t E, const T *__restrict__ u,
                                                        const T *__restrict__ G,
                                                        const T *__restrict__ Dg,
                                                        T *__restrict__ v, int nv,
                                                        const uint32_t *__restrict__ G16,
-                                                       const float *__restrict__ gsc) {
+                                                       const float *__restrict__ gsc,
+                                                       double *dotp = nullptr) {
   using S = AxShape<N>;
   constexpr int NN = S::NN, N3 = S::N3, EPB = S::EPB, RS = S::RS, PS = S::PS;
   // k-planes of G requested together with u, before the first barrier, so that
@@ -158,26 +163,42 @@ __global__ __launch_bounds__(AxShape<N>::BS) void k_ax(int64_t E, const T *__res
     }
   }
   __syncthreads();
-  if (!active) return;
+  if (!DOT && !active) return;
 
   // phase 4: v = D_r^T h_r + D_s^T h_s + D_t^T h_t
-#pragma unroll
-  for (int l = 0; l < N; ++l) {
-    Di[l] = sD[l * N + i];
-    Dj[l] = sD[l * N + j];
-  }
-  T *ve = v + e * N3 + ij;
-#pragma unroll
-  for (int k = 0; k < N; ++k) {
-    T acc = 0;
+  double dot = 0.0;
+  if (active) {
 #pragma unroll
     for (int l = 0; l < N; ++l) {
-      acc += Di[l] * s_a[le][k * PS + j * RS + l];
-      acc += Dj[l] * s_b[le][k * PS + l * RS + i];
-      acc += sD[l * N + k] * wt[l];
+      Di[l] = sD[l * N + i];
+      Dj[l] = sD[l * N + j];
     }
-    if constexpr (GH) acc *= gsc[e];
-    ve[k * NN] = acc;
+    T *ve = v + e * N3 + ij;
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      T acc = 0;
+#pragma unroll
+      for (int l = 0; l < N; ++l) {
+        acc += Di[l] * s_a[le][k * PS + j * RS + l];
+        acc += Dj[l] * s_b[le][k * PS + l * RS + i];
+        acc += sD[l * N + k] * wt[l];
+      }
+      if constexpr (GH) acc *= gsc[e];
+      if constexpr (DOT) dot += (double)uk[k] * (double)acc;
+      ve[k * NN] = acc;
+    }
+  }
+  if constexpr (DOT) {
+    __shared__ double sd[S::BS];
+    sd[tid] = dot;
+    __syncthreads();
+    constexpr int H0 = NN <= 16 ? 8 : NN <= 32 ? 16 : NN <= 64 ? 32 : 64;
+#pragma unroll
+    for (int h = H0; h > 0; h >>= 1) {
+      if (active && ij < h && ij + h < NN) sd[tid] += sd[tid + h];
+      __syncthreads();
+    }
+    if (active && ij == 0) dotp[e] = sd[tid];
   }
 }
 
@@ -408,13 +429,21 @@ static void ax_n(const Level &L, const T *u, T *v, const T *G, const T *D, int n
   if constexpr (sizeof(T) == 4) {
     if (L.G16) {  // FP16 factors
       hipLaunchKernelGGL((k_ax<N, float, true>), dim3(grid), dim3(S::BS), 0, s, L.E, u, G, D, v,
-                         nv, (const uint32_t *)L.G16, (const float *)L.gscale);
+                         nv, (const uint32_t *)L.G16, (const float *)L.gscale, (double *)nullptr);
+      SEM_LAUNCH("k_ax");
+      return;
+    }
+  }
+  if constexpr (sizeof(T) == 8) {
+    if (dotp) {
+      hipLaunchKernelGGL((k_ax<N, T, false, true>), dim3(grid), dim3(S::BS), 0, s, L.E, u, G, D, v, nv,
+                         (const uint32_t *)nullptr, (const float *)nullptr, dotp);
       SEM_LAUNCH("k_ax");
       return;
     }
   }
   hipLaunchKernelGGL((k_ax<N, T, false>), dim3(grid), dim3(S::BS), 0, s, L.E, u, G, D, v, nv,
-                     (const uint32_t *)nullptr, (const float *)nullptr);
+                     (const uint32_t *)nullptr, (const float *)nullptr, (double *)nullptr);
   SEM_LAUNCH("k_ax");
 }
 
@@ -423,14 +452,12 @@ bool ax_sums_x_faces(const Level &L, size_t word, int nv) {
          !gs_in_one_launch(L, word, nv);
 }
 
-bool ax_forms_dot(const Level &L, int nv) { return L.N == 8 && L.ax_variant >= 1 && nv == 1; }
-
 template <typename T>
 void launch_ax(const Level &L, const T *u, T *v, hipStream_t s, int nv, bool xf, double *dotp) {
   if (nv < 1) fail(SEM_EINVAL, "Ax: no right side");
   if (xf && !ax_sums_x_faces(L, sizeof(T), nv)) fail(SEM_EINVAL, "Ax: x-face summation not available here");
-  if (dotp && (sizeof(T) != 8 || !ax_forms_dot(L, nv)))
-    fail(SEM_EINVAL, "Ax: the element shares of (u, Au) need the FP64 p = 7 one-wave kernel");
+  if (dotp && (sizeof(T) != 8 || nv != 1))
+    fail(SEM_EINVAL, "Ax: the element shares of (u, Au) need FP64 and one right side");
   const T *G;
   const T *D;
   if constexpr (sizeof(T) == 8) {

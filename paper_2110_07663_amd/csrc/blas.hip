@@ -5,10 +5,10 @@
 // fixed launch shape and a fixed summation tree (per-thread strided partial
 // sums, an LDS tree per block, then the block partials summed in block
 // order), so results are bitwise repeatable.  The outer Krylov reductions
-// sum the block partials in a second, one-workgroup launch (k_finish); the
-// E-vector coarse CG (a coarsest level other than the assembled p = 1 one)
-// keeps the single-launch form, where the last block to finish, found with a
-// ticket counter, sums them (last_block_sum).
+// sum the partials of more than kTailBlocks blocks in a second, one-workgroup
+// launch (k_finish); those of fewer, and of the E-vector coarse CG (a coarsest
+// level other than the assembled p = 1 one), are summed by the last block to
+// finish, found with a ticket counter (last_block_sum).
 #include <algorithm>
 #include <initializer_list>
 #include <type_traits>
@@ -540,14 +540,15 @@ __device__ inline void block_reduce(double (&acc)[ND], double (*sh)[256]) {
 // Writes this block's partials; returns true in the block that finishes last,
 // after the block partials have been summed in block order into acc (thread 0).
 template <int ND>
-__device__ inline bool last_block_sum(double (&acc)[ND], double *partials, unsigned *counter) {
+__device__ inline bool last_block_sum(double (&acc)[ND], double *partials, unsigned *counter,
+                                      int stride = 8) {
   __shared__ double sh[ND][256];
   __shared__ bool is_last;
   block_reduce<ND>(acc, sh);
   const int tid = threadIdx.x;
   if (tid == 0) {
 #pragma unroll
-    for (int j = 0; j < ND; ++j) partials[blockIdx.x * 8 + j] = sh[j][0];
+    for (int j = 0; j < ND; ++j) partials[blockIdx.x * stride + j] = sh[j][0];
     __threadfence();
     unsigned ticket = atomicAdd(counter, 1u);
     is_last = (ticket == gridDim.x - 1);
@@ -560,7 +561,7 @@ __device__ inline bool last_block_sum(double (&acc)[ND], double *partials, unsig
   for (int b = tid; b < (int)gridDim.x; b += 256) {
 #pragma unroll
     for (int j = 0; j < ND; ++j)
-      acc[j] += __hip_atomic_load(&partials[b * 8 + j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      acc[j] += __hip_atomic_load(&partials[b * stride + j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   block_reduce<ND>(acc, sh);
 #pragma unroll
@@ -581,6 +582,31 @@ __device__ inline void block_partials(double (&acc)[ND], double *partials, int s
   if (threadIdx.x == 0) {
 #pragma unroll
     for (int j = 0; j < ND; ++j) partials[blockIdx.x * stride + j] = sh[j][0];
+  }
+}
+// A reduction over few blocks ends in the block that finishes last, in one launch
+// and with the sums in the same order.  An FCG iteration of small problems, us, best
+// and median of seven runs, second launch against last block: 8 blocks 92.8 (125.1)
+// and 90.5 (117.5), 64 blocks 95.3 (126.3) and 96.0 (122.9); with the last block
+// beyond that, 125 blocks 100.7 and 106.9, 422 blocks 152 and 190 (the tickets
+// serialise on one address).  A null counter: the second launch follows.
+struct Tail {
+  unsigned *counter;
+  double *out;
+};
+constexpr unsigned kTailBlocks = 64;
+static Tail tail_of(const Ctx &c, unsigned nblocks, double *out) {
+  return nblocks <= kTailBlocks ? Tail{c.counter, out} : Tail{nullptr, nullptr};
+}
+template <int ND>
+__device__ inline void block_end(double (&acc)[ND], double *partials, int stride, const Tail &t) {
+  if (!t.counter) {
+    block_partials<ND>(acc, partials, stride);
+    return;
+  }
+  if (last_block_sum<ND>(acc, partials, t.counter, stride) && threadIdx.x == 0) {
+#pragma unroll
+    for (int j = 0; j < ND; ++j) t.out[j] = acc[j];
   }
 }
 // block b's partials at partials[b * stride + j], nd <= stride <= 8, within
@@ -675,7 +701,7 @@ __device__ inline double2 ld2(const float *p, int64_t t) {
 }
 template <int ND, typename V, typename WT>
 __global__ __launch_bounds__(256) void k_wdots(int64_t n, const WT *__restrict__ w, Ptr4 a,
-                                               Ptr4 b, double *partials) {
+                                               Ptr4 b, double *partials, Tail tail) {
   double acc[ND], acc2[ND];
 #pragma unroll
   for (int j = 0; j < ND; ++j) acc[j] = acc2[j] = 0.0;
@@ -697,7 +723,7 @@ __global__ __launch_bounds__(256) void k_wdots(int64_t n, const WT *__restrict__
   }
 #pragma unroll
   for (int j = 0; j < ND; ++j) acc[j] += acc2[j];
-  block_partials<ND>(acc, partials);
+  block_end<ND>(acc, partials, 8, tail);
 }
 
 // FCG step: x += alpha p, r -= alpha q, and (r, r)_w of the new r, with
@@ -727,14 +753,14 @@ __device__ inline double2 ld2n(const float *p, int64_t t) {
   const F2 v = ldn<NT>(reinterpret_cast<const F2 *>(p) + t);
   return make_double2((double)v[0], (double)v[1]);
 }
-template <typename V, typename WT, typename XD = std::false_type, bool NTL = false>
+template <typename V, typename WT, int XD = kAsIs, bool NTL = false>
 __global__ __launch_bounds__(256) void k_fcg_xr(int64_t n, const double *__restrict__ rz,
                                                 const double *__restrict__ pq,
                                                 const WT *__restrict__ w,
                                                 const double *__restrict__ p,
                                                 const double *__restrict__ q, double *__restrict__ x,
                                                 double *__restrict__ r, float *__restrict__ rf,
-                                                double *partials, int pstride, XDev f) {
+                                                double *partials, int pstride, XDev f, Tail tail) {
   const double pqv = *pq;
   const double alpha = pqv > 0.0 ? *rz / pqv : 0.0;
   double acc[1] = {0.0}, acc2 = 0.0;
@@ -742,7 +768,9 @@ __global__ __launch_bounds__(256) void k_fcg_xr(int64_t n, const double *__restr
   const int64_t t0 = xcd_block() * (int64_t)blockDim.x + threadIdx.x;
   for (int64_t t = t0; t < n2; t += (int64_t)gridDim.x * blockDim.x) {
     double2 qv;
-    if constexpr (XD::value) {
+    if constexpr (XD == kAll) {
+      qv = make_double2(read_all(q, 2 * t, f), read_all(q, 2 * t + 1, f));
+    } else if constexpr (XD == kXY) {
       using VT = typename V16<double>::type;
       const VT qq = read_xy(reinterpret_cast<const VT *>(q), t, f);
       qv = make_double2(qq[0], qq[1]);
@@ -777,42 +805,54 @@ __global__ __launch_bounds__(256) void k_fcg_xr(int64_t n, const double *__restr
   }
   if (t0 == 0 && (n & 1)) {
     x[n - 1] += alpha * p[n - 1];
-    r[n - 1] -= alpha * q[n - 1];
+    r[n - 1] -= alpha * (XD == kAll ? read_all(q, n - 1, f) : q[n - 1]);
     if (rf) rf[n - 1] = (float)r[n - 1];
     acc[0] += (double)w[n - 1] * r[n - 1] * r[n - 1];
   }
   acc[0] += acc2;
-  block_partials<1>(acc, partials, pstride);
+  block_end<1>(acc, partials, pstride, tail);
 }
 
 void launch_fcg_xr(const Ctx &c, int64_t n, const double *rz, const double *pq, const double *w,
                    const double *p, const double *q, double *x, double *r, double *out,
                    hipStream_t s, const float *w32, float *rf, const XDefer &xq) {
   const bool al = aligned16(p) && aligned16(q) && aligned16(x) && aligned16(r);
-  const XDev f = xdev<double>(xq);
+  const bool al32 = al && w32 && ((uintptr_t)w32 & 7) == 0;
   unsigned g = red_grid(n);
   int ps = 8;
-  if (xq.on) {
-    if (!(w32 && al && ((uintptr_t)w32 & 7) == 0) || (n & 1))
+  if (xq.on && !xq.all) {
+    if (!al32 || (n & 1))
       fail(SEM_EINVAL, "FCG update: a deferred gather-scatter step needs aligned vectors");
     // one sum, so its partials pack densely: up to 4 kRedBlocks blocks (at
     // 2^24 nodes, 16 waves per SIMD over the launch against 4 at kRedBlocks),
     // with p, w, x and r streamed non-temporally
     g = std::max(1u, std::min(nb(n / 2, 256), 4u * kRedBlocks));
     ps = 1;
-    hipLaunchKernelGGL((k_fcg_xr<std::true_type, float, std::true_type, true>), dim3(g),
-                       dim3(256), 0, s, n, rz, pq, w32, p, q, x, r, rf, c.partials, ps, f);
-  } else if (w32 && al && ((uintptr_t)w32 & 7) == 0)
-    hipLaunchKernelGGL((k_fcg_xr<std::true_type, float>), dim3(g), dim3(256), 0, s, n, rz, pq,
-                       w32, p, q, x, r, rf, c.partials, ps, f);
-  else if (al && aligned16(w))
-    hipLaunchKernelGGL((k_fcg_xr<std::true_type, double>), dim3(g), dim3(256), 0, s, n, rz, pq, w,
-                       p, q, x, r, rf, c.partials, ps, f);
-  else
-    hipLaunchKernelGGL((k_fcg_xr<std::false_type, double>), dim3(g), dim3(256), 0, s, n, rz, pq,
-                       w, p, q, x, r, rf, c.partials, ps, f);
+  }
+  const Tail tail = tail_of(c, g, out);
+#define SEM_XR(V, WT, XD, NT, W, F)                                                                 \
+  hipLaunchKernelGGL((k_fcg_xr<V, WT, XD, NT>), dim3(g), dim3(256), 0, s, n, rz, pq, W, p, q, x, r, rf, \
+                     c.partials, ps, F, tail)
+  if (xq.on && xq.all) {
+    const XDev f = xdev<double>(xq, 1);
+    if (al32)
+      SEM_XR(std::true_type, float, kAll, false, w32, f);
+    else if (al && aligned16(w))
+      SEM_XR(std::true_type, double, kAll, false, w, f);
+    else
+      SEM_XR(std::false_type, double, kAll, false, w, f);
+  } else if (xq.on) {
+    SEM_XR(std::true_type, float, kXY, true, w32, xdev<double>(xq));
+  } else if (al32) {
+    SEM_XR(std::true_type, float, kAsIs, false, w32, XDev{});
+  } else if (al && aligned16(w)) {
+    SEM_XR(std::true_type, double, kAsIs, false, w, XDev{});
+  } else {
+    SEM_XR(std::false_type, double, kAsIs, false, w, XDev{});
+  }
+#undef SEM_XR
   SEM_LAUNCH("k_fcg_xr");
-  launch_finish(1, g, c.partials, out, s, ps);
+  if (!tail.counter) launch_finish(1, g, c.partials, out, s, ps);
 }
 
 void launch_wdots(const Ctx &c, int64_t n, const double *w, int nd, const double *const *a,
@@ -823,10 +863,11 @@ void launch_wdots(const Ctx &c, int64_t n, const double *w, int nd, const double
     pb.p[j] = b[j];
   }
   unsigned g = red_grid(n);
+  const Tail tail = tail_of(c, g, out);
   bool al = true;
   for (int j = 0; j < nd; ++j) al = al && aligned16(a[j]) && aligned16(b[j]);
   if (nd < 1 || nd > 4) fail(SEM_EINVAL, "wdots: at most 4 products");
-#define WD(ND, V, WT, W) hipLaunchKernelGGL((k_wdots<ND, V, WT>), dim3(g), dim3(256), 0, s, n, W, pa, pb, c.partials)
+#define WD(ND, V, WT, W) hipLaunchKernelGGL((k_wdots<ND, V, WT>), dim3(g), dim3(256), 0, s, n, W, pa, pb, c.partials, tail)
 #define WD_ALL(V, WT, W)                                                     \
   do {                                                                       \
     if (nd == 1) WD(1, V, WT, W);                                            \
@@ -843,7 +884,7 @@ void launch_wdots(const Ctx &c, int64_t n, const double *w, int nd, const double
 #undef WD_ALL
 #undef WD
   SEM_LAUNCH("k_wdots");
-  launch_finish(nd, g, c.partials, out, s);
+  if (!tail.counter) launch_finish(nd, g, c.partials, out, s);
 }
 
 // (r, z_j)_w for FP32 z_j (j < ND): the preconditioned residual of the mixed
@@ -855,7 +896,8 @@ template <int ND, typename WT>
 __global__ __launch_bounds__(256) void k_wdots_rz(int64_t n, const WT *__restrict__ w,
                                                   const double *__restrict__ r,
                                                   const float *__restrict__ z0,
-                                                  const float *__restrict__ z1, double *partials) {
+                                                  const float *__restrict__ z1, double *partials,
+                                                  Tail tail) {
   double acc[ND], acc2[ND];
 #pragma unroll
   for (int j = 0; j < ND; ++j) acc[j] = acc2[j] = 0.0;
@@ -878,33 +920,34 @@ __global__ __launch_bounds__(256) void k_wdots_rz(int64_t n, const WT *__restric
   }
 #pragma unroll
   for (int j = 0; j < ND; ++j) acc[j] += acc2[j];
-  block_partials<ND>(acc, partials, ND);
+  block_end<ND>(acc, partials, ND, tail);
 }
 
 void launch_wdots_rz(const Ctx &c, int64_t n, const double *w, const float *w32, const double *r,
                      const float *z0, const float *z1, double *out, hipStream_t s) {
   const int nd = z1 ? 2 : 1;
   const unsigned g = std::max(1u, std::min(nb(n / 2, 256), 8u * kRedBlocks / nd));
+  const Tail tail = tail_of(c, g, out);
   if (!aligned16(r) || ((uintptr_t)z0 & 7) || (z1 && ((uintptr_t)z1 & 7)))
     fail(SEM_EINVAL, "wdots_rz: misaligned vectors");
   if (w32 && ((uintptr_t)w32 & 7) == 0) {
     if (nd == 1)
       hipLaunchKernelGGL((k_wdots_rz<1, float>), dim3(g), dim3(256), 0, s, n, w32, r, z0, z1,
-                         c.partials);
+                         c.partials, tail);
     else
       hipLaunchKernelGGL((k_wdots_rz<2, float>), dim3(g), dim3(256), 0, s, n, w32, r, z0, z1,
-                         c.partials);
+                         c.partials, tail);
   } else {
     if (!aligned16(w)) fail(SEM_EINVAL, "wdots_rz: misaligned weights");
     if (nd == 1)
       hipLaunchKernelGGL((k_wdots_rz<1, double>), dim3(g), dim3(256), 0, s, n, w, r, z0, z1,
-                         c.partials);
+                         c.partials, tail);
     else
       hipLaunchKernelGGL((k_wdots_rz<2, double>), dim3(g), dim3(256), 0, s, n, w, r, z0, z1,
-                         c.partials);
+                         c.partials, tail);
   }
   SEM_LAUNCH("k_wdots_rz");
-  launch_finish(nd, g, c.partials, out, s, nd);
+  if (!tail.counter) launch_finish(nd, g, c.partials, out, s, nd);
 }
 
 // p = z + beta p (FP64 p; z in FP32 on the mixed path), beta from the device

@@ -324,9 +324,7 @@ void launch_start_vector(const Ctx &c, const Level &L, uint64_t seed, double *v,
 // the following launch_gs must then be told (x_in_blocks)
 template <typename T>
 void launch_ax(const Level &L, const T *u, T *v, hipStream_t s, int nv = 1, bool xf = false,
-               double *dotp = nullptr);
-// the FP64 Ax of this level can write each element's share of (u, Au) (dotp[e])
-bool ax_forms_dot(const Level &L, int nv);
+               double *dotp = nullptr);  // dotp[e]: element e's share of (u, Au) (FP64, nv = 1)
 // out = sum of part[0..n) in a fixed order
 void launch_sum_partials(int64_t n, const double *part, double *out, hipStream_t s);
 bool ax_sums_x_faces(const Level &L, size_t word, int nv);

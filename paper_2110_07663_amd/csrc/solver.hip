@@ -472,38 +472,6 @@ static void opA(const Ctx &c, const Level &L, const T *u, T *Au, hipStream_t s, 
   launch_gs<T>(L, Au, s, nv, xf);
 }
 
-// q = A p and (p, q) into *pq (device).  For p consistent and zero on the
-// Dirichlet nodes (every search direction of the CG drivers) the p = 7 FP64 Ax
-// forms (p, q) from its element shares of p^T A_L p; else a weighted dot.
-//
-// q only feeds the FCG update (the dot comes from the element shares), so
-// when the vectors allow, its gather-scatter runs the z pass only and the
-// update takes the x and y steps as it reads q (*xq says so).
-static void opA_dot(const Ctx &c, const Level &L, const double *p, double *q, double *pq,
-                    hipStream_t s, XDefer *xq = nullptr) {
-  if (L.dotpart && ax_forms_dot(L, 1)) {
-    if (xq && L.gs_struct && L.xdefer && L.ydefer && L.w32 &&
-        cheb_can_defer_x<double>(L.N, L.nloc, {p, q, L.w32})) {
-      {
-        ProfScope ps(c, L, SEM_PROF_AX64, s);
-        launch_ax<double>(L, p, q, s, 1, false, L.dotpart);
-      }
-      {
-        ProfScope ps(c, L, SEM_PROF_GS64, s);
-        launch_gs<double>(L, q, s, 1, false, true, true);
-      }
-      *xq = xdefer_of(L, true, false);
-    } else {
-      opA<double>(c, L, p, q, s, 1, L.dotpart);
-    }
-    launch_sum_partials(L.E, L.dotpart, pq, s);
-    return;
-  }
-  opA<double>(c, L, p, q, s);
-  const double *a[1] = {p}, *bb[1] = {q};
-  launch_wdots(c, L.nloc, L.w64, 1, a, bb, pq, s, L.w32);
-}
-
 XDefer xdefer_of(const Level &L, bool y, bool all) {
   XDefer xd;
   xd.on = true;
@@ -529,6 +497,37 @@ XDefer xdefer_of(const Level &L, bool y, bool all) {
 template <typename T>
 static bool update_takes_all(const Level &L, int nv) {
   return L.xdefer && L.ydefer && L.zdefer && gs_in_one_launch(L, sizeof(T), nv);
+}
+
+// q = A p and (p, q) into *pq (device).  For p consistent and zero on the
+// Dirichlet nodes (every search direction of the CG drivers) the FP64 Ax forms (p,
+// q) from its element shares of p^T A_L p (no weighted dot over p and q).
+//
+// q only feeds the FCG update (the dot comes from the element shares), so
+// when the vectors allow, its gather-scatter runs the z pass only and the
+// update takes the x and y steps as it reads q (*xq says so).
+static void opA_dot(const Ctx &c, const Level &L, const double *p, double *q, const double *x,
+                    double *pq, hipStream_t s, XDefer *xq) {
+  if (!L.dotpart) fail(SEM_EINVAL, "(p, Ap): a level without element shares");
+  if (update_takes_all<double>(L, 1)) {
+    ProfScope ps(c, L, SEM_PROF_AX64, s);
+    launch_ax<double>(L, p, q, s, 1, false, L.dotpart);
+    *xq = xdefer_of(L, true, true);
+  } else if (L.gs_struct && L.xdefer && L.ydefer && L.w32 &&
+             cheb_can_defer_x<double>(L.N, L.nloc, {p, q, x, L.w32})) {
+    {
+      ProfScope ps(c, L, SEM_PROF_AX64, s);
+      launch_ax<double>(L, p, q, s, 1, false, L.dotpart);
+    }
+    {
+      ProfScope ps(c, L, SEM_PROF_GS64, s);
+      launch_gs<double>(L, q, s, 1, false, true, true);
+    }
+    *xq = xdefer_of(L, true, false);
+  } else {
+    opA<double>(c, L, p, q, s, 1, L.dotpart);
+  }
+  launch_sum_partials(L.E, L.dotpart, pq, s);
 }
 
 // rs (may be null): apply S to r - rs; r - rs is formed as the VALU FDM reads
@@ -1061,7 +1060,7 @@ static int solve_cg(Ctx &c, const double *b, double *x, double rtol, int maxit, 
     rz_dots(1, ds + 2 * slot);
     while (it < maxit) {
       XDefer xq;
-      opA_dot(c, F, p, q, dpq, s, &xq);
+      opA_dot(c, F, p, q, x, dpq, s, &xq);
       // x, r, (r, r) in one pass (and the V-cycle's FP32 copy of r on the mixed path)
       launch_fcg_xr(c, n, ds + 2 * slot, dpq, F.w64, p, q, x, r, drr, s, F.w32,
                     zf ? F.f_b : nullptr, xq);
