@@ -133,9 +133,12 @@ template void launch_sub<float>(int64_t, const float *, const float *, float *, 
 //         node).  The kernels that read this way take their blocks in
 //         XCD-contiguous order (xcd_block), so the x-neighbour copies they read
 //         mostly come from rows the same XCD reads: its own L2.
-//  kAll   no step was taken: every node sums its up to 8 copies, the x, then the
-//         y, then the z pairs, each as (upper end of the lower element + lower end
-//         of the upper), as the passes do (entry by entry, any N).
+//  kAll   no step was taken: every node sums its up to 8 copies in pairs, each as
+//         (upper end of the lower element + lower end of the upper), entry by entry
+//         for any N.  Direction by direction in the order of the form that more
+//         right sides together would take (the choice depends on their number):
+//         z, y, x where that is the z pass and kXY (zyx), else x, y, z as the passes
+//         do, so that right sides solved together round as they do one at a time.
 // DI: t = dinv times what is read (Jacobi: S is diagonal, and acts on A d).
 enum : int { kAsIs = 0, kXY = 1, kAll = 2 };
 struct XDev {
@@ -144,6 +147,7 @@ struct XDev {
   int y;  // the y step is deferred too (taken before the x step)
   unsigned nez;
   int bc4, bc5;
+  int zyx;         // kAll: z pairs first, x pairs last
   const void *di;  // DI: 1 / diag(A), one right side
 };
 // entry m of several right sides within its own (one right side: no division)
@@ -222,9 +226,13 @@ __device__ inline T read_all(const T *__restrict__ tv, int64_t m, const XDev &f)
     zero = zero || (c == 0 && at == 0 && b0) || (c == f.p && at + 1 == n && b1);
   };
   const int N3 = (int)f.vel, N = (int)f.N, p = (int)f.p;
-  side(0, i, ex, f.nex, N3 - p, f.bc0, f.bc1);
+  const bool zf = f.zyx;  // the direction summed first (0) and last (2): z and x
+  const int sx = N3 - p, sz = (int)(f.nex * f.ney) * N3 - p * N * N;
+  side(0, zf ? k : i, zf ? ez : ex, zf ? f.nez : f.nex, zf ? sz : sx, zf ? f.bc4 : f.bc0,
+       zf ? f.bc5 : f.bc1);
   side(1, j, ey, f.ney, (int)f.nex * N3 - p * N, f.bc2, f.bc3);
-  side(2, k, ez, f.nez, (int)(f.nex * f.ney) * N3 - p * N * N, f.bc4, f.bc5);
+  side(2, zf ? i : k, zf ? ex : ez, zf ? f.nex : f.nez, zf ? sx : sz, zf ? f.bc0 : f.bc4,
+       zf ? f.bc1 : f.bc5);
   const T *__restrict__ at = tv + m;
   T s[2][2][2];  // all eight loads issue; an absent copy reads the node itself
 #pragma unroll
@@ -296,6 +304,7 @@ static XDev xdev(const XDefer &xd, unsigned W = 16 / sizeof(T)) {
   f.nez = (unsigned)xd.nez;
   f.bc4 = xd.bc4;
   f.bc5 = xd.bc5;
+  f.zyx = xd.zyx ? 1 : 0;
   return f;
 }
 

@@ -344,7 +344,8 @@ void launch_sub(int64_t n, const T *a, const T *b, T *y, hipStream_t s);  // y =
 // step (the y and z passes done): each copy on an x-face adds its neighbour's copy
 // as it reads, (p-face + 0-face), and the Dirichlet x-faces read as zero; with y
 // the y step too (the gather-scatter ran its z pass only); with all every step
-// (no gather-scatter ran).  on = false: t is assembled already.
+// (no gather-scatter ran), z first and x last with zyx, else x first.  on = false:
+// t is assembled already.
 // dinv: t is dinv times what is read (Jacobi smoothing of A's output).
 struct XDefer {
   bool on = false;
@@ -352,12 +353,10 @@ struct XDefer {
   int64_t nloc = 0;  // right sides nloc apart
   bool y = false;
   int ney = 0, bc2 = 0, bc3 = 0;
-  bool all = false;
+  bool all = false, zyx = false;
   int nez = 0, bc4 = 0, bc5 = 0;
   const void *dinv = nullptr;
 };
-// the deferred steps of a level (on, and the grid the readers need)
-XDefer xdefer_of(const Level &L, bool y, bool all);
 // whether launch_cheb_* can take the x step for these vectors (16-byte
 // vectors that do not straddle the element rows)
 template <typename T>

@@ -472,7 +472,9 @@ static void opA(const Ctx &c, const Level &L, const T *u, T *Au, hipStream_t s, 
   launch_gs<T>(L, Au, s, nv, xf);
 }
 
-XDefer xdefer_of(const Level &L, bool y, bool all) {
+// the deferred steps of a level (on, and the grid the readers need)
+template <typename T>
+static XDefer xdefer_of(const Level &L, bool y, bool all) {
   XDefer xd;
   xd.on = true;
   xd.nex = L.nex;
@@ -482,6 +484,7 @@ XDefer xdefer_of(const Level &L, bool y, bool all) {
   xd.nloc = L.nloc;
   xd.y = y;
   xd.all = all;
+  xd.zyx = cheb_can_defer_x<T>(L.N, L.nloc, {});  // then the other form is x and y steps
   xd.bc0 = L.bc[0];
   xd.bc1 = L.bc[1];
   xd.bc2 = L.bc[2];
@@ -493,7 +496,8 @@ XDefer xdefer_of(const Level &L, bool y, bool all) {
 
 // Whether the Chebyshev updates of this level sum all copies of a node as they
 // read A's or S's output, with no gather-scatter before them: where that would
-// be one launch of a level whose time is its launches (gs_in_one_launch).
+// be one launch of a level whose time is its launches (gs_in_one_launch).  That
+// depends on the number of right sides, the rounding does not (XDefer::zyx).
 template <typename T>
 static bool update_takes_all(const Level &L, int nv) {
   return L.xdefer && L.ydefer && L.zdefer && gs_in_one_launch(L, sizeof(T), nv);
@@ -512,7 +516,7 @@ static void opA_dot(const Ctx &c, const Level &L, const double *p, double *q, co
   if (update_takes_all<double>(L, 1)) {
     ProfScope ps(c, L, SEM_PROF_AX64, s);
     launch_ax<double>(L, p, q, s, 1, false, L.dotpart);
-    *xq = xdefer_of(L, true, true);
+    *xq = xdefer_of<double>(L, true, true);
   } else if (L.gs_struct && L.xdefer && L.ydefer && L.w32 &&
              cheb_can_defer_x<double>(L.N, L.nloc, {p, q, x, L.w32})) {
     {
@@ -523,7 +527,7 @@ static void opA_dot(const Ctx &c, const Level &L, const double *p, double *q, co
       ProfScope ps(c, L, SEM_PROF_GS64, s);
       launch_gs<double>(L, q, s, 1, false, true, true);
     }
-    *xq = xdefer_of(L, true, false);
+    *xq = xdefer_of<double>(L, true, false);
   } else {
     opA<double>(c, L, p, q, s, 1, L.dotpart);
   }
@@ -622,10 +626,10 @@ static void opS(const Ctx &c, const Level &L, const T *r, T *z, hipStream_t s, i
   }
   if (asm_mode) return;  // the overlap sum already produced a consistent, masked vector
   if (all) {  // no gather-scatter: the update sums the copies as it reads
-    *xd = xdefer_of(L, true, true);
+    *xd = xdefer_of<T>(L, true, true);
     return;
   }
-  if (defer) *xd = xdefer_of(L, L.ydefer, false);
+  if (defer) *xd = xdefer_of<T>(L, L.ydefer, false);
   ProfScope ps(c, L, sizeof(T) == 8 ? SEM_PROF_GS64 : SEM_PROF_GS32, s);
   launch_gs<T>(L, z, s, nv, fxf, defer, defer && L.ydefer);
 }
@@ -651,12 +655,12 @@ static void chebyshev(const Ctx &c, Level &L, const T *b, T *x, bool x_zero, hip
   auto opA_read = [&](const T *u, std::initializer_list<const void *> ps) {
     XDefer xd;
     if (update_takes_all<T>(L, nv)) {
-      xd = xdefer_of(L, true, true);
+      xd = xdefer_of<T>(L, true, true);
       ProfScope pr(c, L, sizeof(T) == 8 ? SEM_PROF_AX64 : SEM_PROF_AX32, s);
       launch_ax<T>(L, u, w, s, nv, false, nullptr);
     } else if (L.gs_struct && L.xdefer && L.ydefer && cheb_can_defer_x<T>(L.N, n, ps) &&
                cheb_can_defer_x<T>(L.N, n, {w, dinv})) {
-      xd = xdefer_of(L, true, false);
+      xd = xdefer_of<T>(L, true, false);
       {
         ProfScope pr(c, L, sizeof(T) == 8 ? SEM_PROF_AX64 : SEM_PROF_AX32, s);
         launch_ax<T>(L, u, w, s, nv, false, nullptr);
