@@ -474,13 +474,29 @@ __global__ void k_gs_yz(T *__restrict__ v, GsGrid g, int64_t E, int64_t ny_t, in
 // 0: x, 1: y, 2: z): along a shared direction a node is a face of the element
 // grid (0..n), along another an element and an interior node (1..p-1).
 //
-// For levels whose passes are launches and little else: apply_A with three
-// launches against this one, FP64 / FP32: p = 3, 5^3 elements 13.1 / 9.2 and
-// 15.7 / 9.2 us; p = 7, 9^3 (104,000 boundary nodes) 14.4 / 14.8 and 15.6 / 11.0;
-// p = 9, 9^3 (178,000) 21.8 / 21.1 and 17.8 / 15.1.  Above, the sets reach the
-// same lines from different XCDs, and the passes, which walk the elements in
-// order, are faster: p = 7, 13^3 (304,000) 25.5 / 27.0 and 17.8 / 19.0.
-constexpr int64_t kGsAll64 = 120000, kGsAll32 = 180000;  // boundary nodes times right sides
+// For levels whose passes are launches and little else (p = 3, 5^3 elements:
+// apply_A with three launches against this one 13.1 / 9.2 us in FP64, 15.7 / 9.2 in
+// FP32).  Above, the sets reach the same lines from different XCDs, and the passes,
+// which walk the elements in order, are faster.  The limits are where apply_A on
+// cubes stops gaining, in boundary nodes times right sides.  FP64, passes against
+// one launch, us: p = 2, 31,800 nodes 13.8 / 11.2, 60,900 13.1 / 13.5, 103,800
+// 15.0 / 18.7; p = 3, 84,900 12.9 / 11.6, 163,000 16.4 / 17.7; p = 4, 71,000
+// 13.2 / 12.4, 89,600 13.2 / 13.8; p = 5, 68,700 13.1 / 12.1, 90,400 13.5 / 14.0;
+// p = 6, 53,600 13.1 / 12.3, 75,300 13.1 / 13.5; p = 7, 74,600 15.2 / 13.7, 104,700
+// 14.4 / 14.9; p = 8, 67,500 13.7 / 13.4, 99,000 14.7 / 15.5; p = 9, 86,500
+// 15.4 / 14.9, 126,900 16.2 / 16.7; p = 10, 69,500 16.8 / 16.3, 107,900 17.9 / 18.0.
+// FP32, whose passes are three launches: p = 4, 164,000 16.4 / 15.4; p = 7, 187,100
+// 16.1 / 14.4, 304,100 18.5 / 18.9; p = 3, 163,000 16.3 / 15.6, 278,400 17.1 / 23.8.
+static int64_t gs_all_limit(int p, size_t word) {
+  if (word == 4) return 180000;
+  return p == 2 ? 50000 : p == 3 || p >= 9 ? 90000 : 75000;
+}
+// The Chebyshev and FCG updates that sum the copies as they read save that launch
+// too and gain for longer.  A Cheby(2) step with the passes against that form, us: RAS
+// in FP64 p = 5, 116,400 nodes 92.2 / 87.1, 146,900 104.8 / 105.1, p = 7, 141,900
+// 99.8 / 94.5, 187,100 119.3 / 119.7; in FP32 p = 3, 163,000 70.9 / 71.5, p = 5,
+// 182,300 74.2 / 73.6, 269,300 82.4 / 85.3.
+constexpr int64_t kReadAll64 = 120000, kReadAll32 = 180000;
 struct GsSets {
   unsigned end[7];  // cumulative thread counts of the sets 1..7
 };
@@ -552,12 +568,18 @@ static int64_t gs_set_nodes(const Level &L, int set) {
   for (int d = 0; d < 3; ++d) cnt *= (set >> d) & 1 ? n[d] + 1 : n[d] * (L.p - 1);
   return cnt;
 }
-bool gs_in_one_launch(const Level &L, size_t word, int nv) {
+// boundary nodes times right sides up to `limit`
+static bool gs_small(const Level &L, int nv, int64_t limit) {
   if (!L.gs_struct || L.gs_all == 0) return false;
   int64_t total = 0;
   for (int m = 1; m < 8; ++m) total += gs_set_nodes(L, m);
-  if (L.gs_all == 1) return total * nv < ((int64_t)1 << 31);
-  return total * nv <= (word == 8 ? kGsAll64 : kGsAll32);
+  return total * nv <= (L.gs_all == 1 ? INT32_MAX : limit);  // 1: on every level
+}
+bool gs_in_one_launch(const Level &L, size_t word, int nv) {
+  return gs_small(L, nv, gs_all_limit(L.p, word));
+}
+bool gs_read_unassembled(const Level &L, size_t word, int nv) {
+  return gs_small(L, nv, word == 8 ? kReadAll64 : kReadAll32);
 }
 
 template <typename T>

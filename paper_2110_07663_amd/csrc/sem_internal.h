@@ -316,6 +316,9 @@ void launch_gs(const Level &L, T *v, hipStream_t s, int nv = 1, bool x_in_blocks
 // whether launch_gs takes all passes of this level in one launch (nv vectors of
 // word bytes); a producer then leaves the x-faces inside its workgroups to it
 bool gs_in_one_launch(const Level &L, size_t word, int nv);
+// whether the updates sum the copies of A's or S's output as they read it, with
+// no gather-scatter before them
+bool gs_read_unassembled(const Level &L, size_t word, int nv);
 void launch_weights(const Level &L, hipStream_t s);
 void launch_start_vector(const Ctx &c, const Level &L, uint64_t seed, double *v, hipStream_t s);
 

@@ -495,12 +495,12 @@ static XDefer xdefer_of(const Level &L, bool y, bool all) {
 }
 
 // Whether the Chebyshev updates of this level sum all copies of a node as they
-// read A's or S's output, with no gather-scatter before them: where that would
-// be one launch of a level whose time is its launches (gs_in_one_launch).  That
-// depends on the number of right sides, the rounding does not (XDefer::zyx).
+// read A's or S's output, with no gather-scatter before them: levels whose time
+// is their launches (gs_read_unassembled).  That depends on the number of right
+// sides, the rounding does not (XDefer::zyx).
 template <typename T>
 static bool update_takes_all(const Level &L, int nv) {
-  return L.xdefer && L.ydefer && L.zdefer && gs_in_one_launch(L, sizeof(T), nv);
+  return L.xdefer && L.ydefer && L.zdefer && gs_read_unassembled(L, sizeof(T), nv);
 }
 
 // q = A p and (p, q) into *pq (device).  For p consistent and zero on the
