@@ -1017,13 +1017,17 @@ void mf32_launch(const Ctx &c, const Level &L, const float *r, const float *rs, 
   if (xin & ~15 || which == 3 || (ys && which == 0) || (xf && which == 1))
     fail(SEM_EINVAL, "FDM: unknown form of the deferred gather-scatter steps");
   if (which == 2 && !rs) fail(SEM_EINVAL, "FDM: no subtrahend to take the x step");
-  const bool x8 = xf && L.xgroup == 8;
 #define SEM_MF_LAUNCH(RS, XS, YS, XF) mf32_launch_x<P, RS, XS, YS, XF, OP>(c, L, r, rs, z, s, nv)
-#define SEM_MF_XF(RS, XS, YS)                     \
-  do {                                            \
-    if (x8) SEM_MF_LAUNCH(RS, XS, YS, 8);         \
-    else if (xf) SEM_MF_LAUNCH(RS, XS, YS, 4);    \
-    else SEM_MF_LAUNCH(RS, XS, YS, 0);            \
+#define SEM_MF_XF(RS, XS, YS)                          \
+  do {                                                 \
+    if constexpr (P <= kX8MaxP) {                      \
+      if (xf && L.xgroup == 8) {                       \
+        SEM_MF_LAUNCH(RS, XS, YS, 8);                  \
+        break;                                         \
+      }                                                \
+    }                                                  \
+    if (xf) SEM_MF_LAUNCH(RS, XS, YS, 4);              \
+    else SEM_MF_LAUNCH(RS, XS, YS, 0);                 \
   } while (0)
   if (rs) {
     if (which == 1) fail(SEM_EINVAL, "FDM: the x step is taken on the subtrahend only");

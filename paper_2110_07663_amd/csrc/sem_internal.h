@@ -28,6 +28,7 @@ void check_hip(hipError_t e, const char *what, const char *file, int line);
 #define SEM_LAUNCH(what) ::sem::check_hip(hipGetLastError(), what, __FILE__, __LINE__)
 
 constexpr int kMaxP = 10;      // highest supported polynomial degree
+constexpr int kX8MaxP = 7;     // highest degree with x-face sums over 8 elements per workgroup
 constexpr int kMaxLevels = 8;
 constexpr int kMaxArnoldi = 16;
 
@@ -108,7 +109,7 @@ struct Level {
   int bc[6] = {0, 0, 0, 0, 0, 0};
   bool gs_struct = true;             // false: the sorted-numbering segments (perm/off)
   bool xfuse = true;                 // the p = 7 Ax sums x-faces inside its workgroups
-  int xgroup = 4;                    // elements along x per workgroup that sums its x-faces
+  int xgroup = 4;                    // elements along x per workgroup that sums its x-faces (4 or 8)
   int gs_yz = -1;                    // y and z passes in one launch: 1 yes, 0 no, -1 FP64 only
   int gs_all = -1;                   // all passes in one launch: 1 yes, 0 no, -1 small levels only
   bool xdefer = true;                // Chebyshev updates may take the x step of S's gather-scatter

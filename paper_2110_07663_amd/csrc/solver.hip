@@ -292,6 +292,27 @@ static void layout(Ctx &c, const sem_mesh *m, Arena &A, SetupScratch &sc) {
   sc.gs.cap = gsb;
 }
 
+// Elements along x in a workgroup that sums the x-faces it shares (Ax at p = 7, FDM):
+// 8 or 4.  The gather-scatter's x pass, which touches a cache line per face node, is
+// left with the faces between groups: at 32^3, p = 7 14.5 us with groups of 8, 28
+// with 4 in FP64, 7.3 and 12.4 in FP32.  8 needs
+// - whole groups in the line;
+// - p <= 7: from p = 8 a group of 8 takes more than 50 KB of LDS in the FDM, and with
+//   its waves the occupancy goes;
+// - even shares: the fullest of the 256 CUs gets whole groups, and 4680 elements
+//   leave it 24 in groups of 8 and 20 in groups of 4.  Up to 1/32 more is taken.
+// 8 against 4, us: product at 32^3, p = 7 226 / 236 in FP64, 121 / 127 in FP32; FP32
+// Schwarz at 32^3 p = 3 29.2 / 29.1, p = 5 45.7 / 47.0, p = 7 87.2 / 91.0, with FP16
+// operands 29.4 / 31.8, 43.4 / 46.6, 72.5 / 76.6; at 24^3 p = 8 59.1 / 56.8, p = 9
+// 77.0 / 74.5, with FP16 operands 50.6 / 47.5 and 63.9 / 61.0; at 40x9x13 (the 4680
+// elements) p = 4 14.9 / 14.5, p = 7 22.8 / 22.0, product 25.4 / 24.5.
+static int x_group(int nex, int64_t E, int p, int asked) {
+  if (nex % 8 != 0 || p > kX8MaxP || asked == 4) return 4;
+  if (asked == 8) return 8;
+  const int64_t cus = 256, of8 = (E / 8 + cus - 1) / cus * 8, of4 = (E / 4 + cus - 1) / cus * 4;
+  return 32 * of8 <= 33 * of4 ? 8 : 4;
+}
+
 static void init_ctx(Ctx &c, const sem_mesh *m, int p, const int8_t *bc, const sem_opts *o) {
   c.nex = m->nex;
   c.ney = m->ney;
@@ -330,13 +351,10 @@ static void init_ctx(Ctx &c, const sem_mesh *m, int p, const int8_t *bc, const s
       // SEM_AX_XFUSE=0: the p = 7 Ax leaves every x-face to the gather-scatter
       const char *xfv = getenv("SEM_AX_XFUSE");
       L.xfuse = !(xfv && xfv[0] == '0');
-      // Elements along x in a workgroup that sums the x-faces it shares (Ax at p = 7,
-      // FDM): 8 where they divide the line, else 4; SEM_XGROUP=4 keeps 4.  The
-      // gather-scatter's x pass, which touches a cache line per face node, is left
-      // with the faces between groups: at 32^3 (p = 7) 14.5 us with groups of 8, 28 with
-      // 4 in FP64 (the product 224 and 236), 7.3 and 12.4 in FP32 (Schwarz 99.7, 102.6).
+      // SEM_XGROUP=4 / 8: elements along x in a workgroup that sums the x-faces it
+      // shares (8 only where the groups fit, see x_group)
       const char *xgv = getenv("SEM_XGROUP");
-      L.xgroup = m->nex % 8 == 0 && !(xgv && xgv[0] == '4') ? 8 : 4;
+      L.xgroup = x_group(m->nex, E, L.p, xgv ? atoi(xgv) : 0);
       // SEM_GS_XDEFER=0: the gather-scatter after an FDM that only feeds a
       // Chebyshev update takes its x step itself
       const char *xdv = getenv("SEM_GS_XDEFER");
