@@ -363,8 +363,8 @@ __global__ __launch_bounds__(256) void k_fdm_mf64(int64_t E, int nex, int ney, i
   }
 }
 
-// Four waves per element up to half a wave per SIMD (1024) and from p = 7, where an
-// element has enough slots of lines to deal out.  With the assembly, one against
+// Four waves per element up to 640 elements (2.5 waves per SIMD) and from p = 7,
+// where an element has enough slots of lines to deal out.  With the assembly, one against
 // four: 512 elements p = 7 14.9 / 13.3 us, p = 9 17.3 / 15.4, p = 10 22.6 / 18.7, p =
 // 5 9.8 / 10.4; 768 elements p = 7 16.6 / 16.5; 1728 elements p = 9 32.4 / 34.4.
 constexpr int kWideP = 7;
@@ -376,7 +376,7 @@ void mf64_launch(const Ctx &c, const Level &L, const double *r, const double *rs
   using F = Md<P, ASM>;
   RasGrid W{0};
   for (int f = 0; f < 6; ++f) W.bcm |= (L.bc[f] ? 1 : 0) << f;
-  const bool wide = P >= kWideP && L.E * nv <= kWideElements;
+  const bool wide = P >= kWideP && (c.fdm_mf64_waves ? c.fdm_mf64_waves == 4 : L.E * nv <= kWideElements);
   const int epb = wide ? F::WAVES / 4 : F::WAVES;
   const dim3 grid((unsigned)((L.E + epb - 1) / epb * nv)), block(64 * F::WAVES);
   constexpr int WPE = P >= kWideP ? 4 : 1;
