@@ -675,11 +675,11 @@ __global__ __launch_bounds__(256) void k_asm_sum(int64_t E, int nex, int ney, in
 }
 
 template <int P, typename T>
-static void asm_sum(const Level &L, const T *box, T *z, hipStream_t s) {
+static void asm_sum(const Ctx &c, const Level &L, const T *box, T *z, hipStream_t s) {
   constexpr int64_t PB = P + 3;
   // a block's reads span two planes, two lines and a few elements of boxes
   const int64_t span = 2 * ((int64_t)L.nex * L.ney + L.nex + 1) + 256;
-  const bool wide = span * PB * PB * PB * (int64_t)sizeof(T) >= 0x7FFFFF00;
+  const bool wide = c.asm_wide || span * PB * PB * PB * (int64_t)sizeof(T) >= 0x7FFFFF00;
   int bcm = 0;
   for (int f = 0; f < 6; ++f) bcm |= (L.bc[f] ? 1 : 0) << f;
   const dim3 grid((unsigned)((L.nloc + 255) / 256)), block(256);
@@ -695,15 +695,15 @@ static void asm_sum(const Level &L, const T *box, T *z, hipStream_t s) {
 template <typename T>
 void launch_asm_sum(const Ctx &c, const Level &L, const T *box, T *z, hipStream_t s) {
   switch (L.p) {
-    case 2: asm_sum<2, T>(L, box, z, s); break;
-    case 3: asm_sum<3, T>(L, box, z, s); break;
-    case 4: asm_sum<4, T>(L, box, z, s); break;
-    case 5: asm_sum<5, T>(L, box, z, s); break;
-    case 6: asm_sum<6, T>(L, box, z, s); break;
-    case 7: asm_sum<7, T>(L, box, z, s); break;
-    case 8: asm_sum<8, T>(L, box, z, s); break;
-    case 9: asm_sum<9, T>(L, box, z, s); break;
-    case 10: asm_sum<10, T>(L, box, z, s); break;
+    case 2: asm_sum<2, T>(c, L, box, z, s); break;
+    case 3: asm_sum<3, T>(c, L, box, z, s); break;
+    case 4: asm_sum<4, T>(c, L, box, z, s); break;
+    case 5: asm_sum<5, T>(c, L, box, z, s); break;
+    case 6: asm_sum<6, T>(c, L, box, z, s); break;
+    case 7: asm_sum<7, T>(c, L, box, z, s); break;
+    case 8: asm_sum<8, T>(c, L, box, z, s); break;
+    case 9: asm_sum<9, T>(c, L, box, z, s); break;
+    case 10: asm_sum<10, T>(c, L, box, z, s); break;
     default: fail(SEM_EUNSUPPORTED, "ASM: unsupported degree");
   }
 }

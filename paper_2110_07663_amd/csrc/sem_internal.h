@@ -276,6 +276,7 @@ struct Ctx {
   bool fdm_mf32 = true;   // FP32 RAS local solves on the matrix cores (fdm_mf32.hip)
   bool fdm_mf64 = true;   // FP64 Schwarz local solves on the matrix cores (fdm_mf64.hip)
   int fdm_mf64_waves = 0; // wavefronts per element there from p = 7: 1 or 4, 0 by the element count
+  bool asm_wide = false;  // ASM overlap sum by plain loads (planes of boxes past 2 GiB: always)
   int fdm_mf32_chain = 1; // elements per wavefront there (1 or 2), next one's loads ahead
   bool fdm_mf16 = true;   // FP16 / BF16 RAS operands in that kernel's 4x4x4 form
   bool fdm_xstep = true;  // that kernel takes the x step of A's gather-scatter as it reads

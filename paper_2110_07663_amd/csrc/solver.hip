@@ -394,6 +394,8 @@ static void init_ctx(Ctx &c, const sem_mesh *m, int p, const int8_t *bc, const s
   c.fdm_mf64 = !(f64 && f64[0] == '0');
   const char *f64w = getenv("SEM_FDM_MF64_WAVES");
   c.fdm_mf64_waves = f64w && (f64w[0] == '1' || f64w[0] == '4') ? f64w[0] - '0' : 0;
+  const char *aw = getenv("SEM_ASM_WIDE");
+  c.asm_wide = aw && aw[0] == '1';
   const char *f16 = getenv("SEM_FDM_MF16");
   c.fdm_mf16 = !(f16 && f16[0] == '0');
   const char *fch = getenv("SEM_FDM_MF32_CHAIN");
