@@ -22,7 +22,11 @@
 // update the rest, scale its block column).  Dirichlet rows of the stencil are
 // identity rows, so they need no special case.  A pivot below 1e-12 of its
 // row's diagonal (a numerically singular level, e.g. all-Neumann) is reported
-// and the caller keeps the CG.
+// and the caller keeps the CG.  The diagonal is that of T_k, to which the blocks
+// before k have contributed and the planes inside k have not: boxes more than about
+// 5e6 times thinner in z than wide, with Neumann z-faces, fail the test in blocks of
+// several planes (smallest pivot 2.2e-11 of its diagonal at 1e6, in single planes
+// 0.87 at any ratio), so a level that fails is factored once more in single planes.
 //
 // Storage: per block G [Mp][Mp], H [mp][Mp] and J [Mp][mp] in FP64, Mp = the
 // nodes of a block and mp = those of a plane rounded up to 32 (identity / zero
@@ -52,14 +56,16 @@ static inline int64_t padded(int64_t m) { return (m + kGB - 1) / kGB * kGB; }
 // nodes: one launch instead of 5; 9^3: one instead of 9 (32 us of an FP64 V-cycle's
 // 412 at 9x7x8, p = 9: now 391); 17^3: 3 instead of 17; 33^3 keeps single planes
 // (pairs: 1.3 % of the 32^3 solve for 30 ms of setup).
-BtShape coarse_direct_shape(int64_t nx, int64_t ny, int64_t nz, bool f32) {
+// planes > 0: that many instead.
+BtShape coarse_direct_shape(int64_t nx, int64_t ny, int64_t nz, bool f32, int planes) {
   BtShape best{};
   double best_us = 0.0;
   const int64_t m = nx * ny, mp = padded(m), one = 3 * nz * mp * mp;
   const int64_t most = std::max<int64_t>((int64_t)64 << 20, one + one / 2);
   // SEM_COARSE_PLANES=g: that many planes per block
   const char *gv = getenv("SEM_COARSE_PLANES");
-  const int64_t forced = gv ? std::min<int64_t>(std::max(atoi(gv), 1), nz) : 0;
+  if (planes == 0 && gv) planes = std::max(atoi(gv), 1);
+  const int64_t forced = std::min<int64_t>(planes, nz);
   for (int64_t g = 1; g <= nz; ++g) {
     const int64_t B = (nz + g - 1) / g, Mp = padded(g * m), c = B / 2;
     const int64_t entries = B * (Mp * Mp + 2 * mp * Mp);
@@ -416,7 +422,8 @@ struct BtBlocks {
   int rows(int k) const { return planes(k) * q.m; }
 };
 
-void coarse_direct_setup(CoarseSolver &S, int64_t nx, int64_t ny, int64_t nz, hipStream_t s) {
+// factors the level in the blocks S.shape; S.direct: no pivot failed its test
+static void bt_factor(CoarseSolver &S, int64_t nx, int64_t ny, int64_t nz, hipStream_t s) {
   const BtBlocks<double> D{S.dG, S.dH, S.dJ, S.shape};
   const BtShape &q = S.shape;
   const int B = q.B, c = B / 2, Mp = q.Mp, mp = q.mp, nbk = Mp / kGB;
@@ -470,6 +477,13 @@ void coarse_direct_setup(CoarseSolver &S, int64_t nx, int64_t ny, int64_t nz, hi
   SEM_HIP(hipMemcpyAsync(&flag, S.dflag, sizeof(int), hipMemcpyDeviceToHost, s));
   SEM_HIP(hipStreamSynchronize(s));
   S.direct = flag == 0;
+}
+
+void coarse_direct_setup(CoarseSolver &S, int64_t nx, int64_t ny, int64_t nz, hipStream_t s) {
+  bt_factor(S, nx, ny, nz, s);
+  if (S.direct || S.shape.g == 1) return;
+  S.shape = coarse_direct_shape(nx, ny, nz, S.fG != nullptr, 1);
+  bt_factor(S, nx, ny, nz, s);
 }
 
 template <int NV, typename MT>

@@ -475,7 +475,8 @@ struct CoarseRhs {
 void coarse_solve_assembled(Ctx &c, Level &C, double tol, int maxit, hipStream_t s, int nv,
                             CoarseRhs u, double *x, float *xf);
 void coarse_release(CoarseSolver &S);
-BtShape coarse_direct_shape(int64_t nx, int64_t ny, int64_t nz, bool f32);
+BtShape coarse_direct_shape(int64_t nx, int64_t ny, int64_t nz, bool f32, int planes = 0);
+// (buffers hold the blocks of S.shape and those of single planes)
 void coarse_direct_setup(CoarseSolver &S, int64_t nx, int64_t ny, int64_t nz, hipStream_t s);
 // nv right sides, S.n apart in b, x and the work vector S.dy
 void coarse_direct_apply(const CoarseSolver &S, const double *b, double *x, hipStream_t s,

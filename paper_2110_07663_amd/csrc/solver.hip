@@ -259,7 +259,9 @@ static void layout(Ctx &c, const sem_mesh *m, Arena &A, SetupScratch &sc) {
       S.dflag = nullptr;
       if (want) {
         S.shape = coarse_direct_shape(nx, ny, nz, f32);
-        const int64_t Mp = S.shape.Mp, ng = S.shape.B * Mp * Mp, nh = S.shape.B * Mp * S.shape.mp;
+        const int64_t Mp = S.shape.Mp;  // (single planes: the second attempt of the setup)
+        const int64_t ng = std::max(S.shape.B * Mp * Mp, nz * plane * plane);
+        const int64_t nh = std::max(S.shape.B * Mp * S.shape.mp, nz * plane * plane);
         S.dG = A.take<double>((size_t)ng);
         S.dH = A.take<double>((size_t)nh);
         S.dJ = A.take<double>((size_t)nh);
