@@ -471,7 +471,7 @@ struct CoarseRhs {
   const void *p = nullptr;
   bool f32 = false;
 };
-// xf (may be null): the solution goes there in FP32 instead of to c.cx
+// xf (may be null): the solution goes there in FP32 instead of to x
 void coarse_solve_assembled(Ctx &c, Level &C, double tol, int maxit, hipStream_t s, int nv,
                             CoarseRhs u, double *x, float *xf);
 void coarse_release(CoarseSolver &S);

@@ -211,7 +211,7 @@ static void layout(Ctx &c, const sem_mesh *m, Arena &A, SetupScratch &sc) {
     c.projAW = A.take<double>(F.nloc);
   }
   const Level &C = c.lev[c.nlev - 1];
-  c.cx = A.take<double>(nv * C.nloc);
+  c.cx = A.take<double>(C.nloc);
   c.cr = A.take<double>(C.nloc);
   c.cz = A.take<double>(C.nloc);
   c.cp = A.take<double>(C.nloc);
