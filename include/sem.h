@@ -110,7 +110,9 @@ typedef struct {
                               /* blocks hold several planes, and as many floats under an  */
                               /* FP32 smoother, whose sweeps read FP32 copies; falls back */
                               /* to the PCG if the level is singular), -1 library         */
-                              /* default: 1 when the doubles take <= 4 GiB                */
+                              /* default: 1 when the doubles of single planes take        */
+                              /* <= 4 GiB (blocks of several take up to 1.5 times those,  */
+                              /* or up to 0.5 GiB)                                        */
   int32_t proj_max;           /* > 0: sem_solve starts from the A-conjugate projection of */
                               /* b onto up to proj_max prior solutions (successive right  */
                               /* sides, Sec. 3.2 / 4.2) and stops at ||r|| <= rtol ||b||; */

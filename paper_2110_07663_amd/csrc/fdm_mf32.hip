@@ -202,10 +202,11 @@ struct BufF32 {
 // SIMD otherwise drift into the same phase and the matrix pipe and the LDS take
 // turns (the kernel without its loads, p = 7, 32^3: 74 us, without its products 43,
 // with both 75); with the priorities a wave between two contractions overtakes
-// those inside one.  Measured at 32^3, p = 7, FP32: 74.8 -> 64.9 us with assembled
-// input (with the line order of the last exchange, below, 4 of them); raising the
-// products instead gives the same there, but 92.2 against 90.2 us on average over
-// the three forms of a smoothing step (101.4 before).
+// those inside one.  Measured at 32^3, p = 7, FP32, groups of 4 along x, with the
+// line order of the last exchange below (4 us of the first): assembled input 74.0 ->
+// 63.9 us, A's x and y steps taken 88 -> 77, residual form 107.5 -> 105.0.  Raising
+// the products instead gives the same for the first, but 92.2 against 90.2 us on
+// average over the launches of a smoothing step in one run.
 constexpr int kPrioMatrix = 0, kPrioMove = 2, kPrioLds = 3;
 
 // forward contraction of one slot: acc[g][i] = sum_k v[k] S[k][4g + i]

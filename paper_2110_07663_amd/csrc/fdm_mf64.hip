@@ -17,14 +17,14 @@
 // together exceed the scalar cache) stalled it for three quarters of its time:
 // 63 us for 8000 elements against 38.7 us here (RAS; its HBM
 // traffic alone would take 16 us).  What bounds it now: the matrix pipe is busy
-// 48 % of the cycles (62 % of that on real entries, the rest pads 10 modes and
+// 48 % of the cycles (68 % of that on real entries, the rest pads 10 modes and
 // nodes to 12 and 100 lines to 112) and the vector pipe most of the others
 // (addresses, the 1000 reciprocals of the eigenvalue sums).
 //
 // The passes run z, y, x forward and x, y, z backward, so that the first
 // reads and the last writes address consecutive nodes of the E-vector across
 // the 16 lines.  One wavefront per element, four per workgroup, no workgroup
-// barriers.
+// barriers; on small meshes four per element (WPE below).
 #include "sem_internal.h"
 
 namespace sem {
