@@ -68,7 +68,13 @@ __global__ __launch_bounds__(AxShape<N>::BS) void k_ax(int64_t E, const T *__res
   // quarter of the planes: p = 6 45.1 / 44.0 and 83.4 / 79.9 us, p = 8 55.7 / 52.8
   // and 110 / 103, p = 9 48.2 / 43.6 and 74.9 / 69.6; more planes cost registers
   // (p = 9 with all: 45.3 and 76.4); no gain below p = 5, nor at p = 10 in FP64.
-  constexpr int PF = N >= 6 && !(N == 11 && sizeof(T) == 8) ? (N + 3) / 4 : 0;
+  // None where the registers cost more than the wait: p = 5 in FP32 (32^3 58.2 none,
+  // 60.0 a quarter; with FP16 factors 24^3 28.8 and 29.9) and p = 9 with FP16 factors
+  // (16^3 37.5 and 39.0, 24^3 100.5 and 109.0); p = 6, 8, 10 gain with them (24^3, 24^3,
+  // 20^3 38.1 / 37.5, 69.2 / 67.9, 75.9 / 74.5), and so does p = 5 in FP64 (24^3 58.1 / 56.8).
+  constexpr bool kNoPF = N < 6 || (N == 11 && sizeof(T) == 8) || (N == 6 && sizeof(T) == 4) ||
+                         (N == 10 && GH);
+  constexpr int PF = kNoPF ? 0 : (N + 3) / 4;
   __shared__ T sD[NN];
   __shared__ T s_a[EPB][N * PS];
   __shared__ T s_b[EPB][N * PS];
