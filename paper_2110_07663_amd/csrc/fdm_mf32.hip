@@ -206,7 +206,8 @@ struct BufF32 {
 // line order of the last exchange below (4 us of the first): assembled input 74.0 ->
 // 63.9 us, A's x and y steps taken 88 -> 77, residual form 107.5 -> 105.0.  Raising
 // the products instead gives the same for the first, but 92.2 against 90.2 us on
-// average over the launches of a smoothing step in one run.
+// average over the launches of a smoothing step in one run.  The 16-bit forms, whose
+// products are a third as many, are as fast without them to 2 % either way.
 constexpr int kPrioMatrix = 0, kPrioMove = 2, kPrioLds = 3;
 
 // forward contraction of one slot: acc[g][i] = sum_k v[k] S[k][4g + i]
